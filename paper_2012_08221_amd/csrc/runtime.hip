@@ -1518,7 +1518,10 @@ int pdfx_eval_set_xfx(const pdfx_set *s, int prec, const int32_t *pids, int32_t 
     const LaunchShape ls = s->shape[prec];
     const int64_t tile_pts = (int64_t)ls.block * ls.ppt;
     const int64_t ntiles = (n_pts + tile_pts - 1) / tile_pts;
-    int64_t tpi = s->tiles_per_item[prec];
+    // runs of tiles short enough to give every compute unit a few items
+    // (101 members of 4000 points in runs of 4 tiles are 101 items: 167 us,
+    // 62 us as 404)
+    int64_t tpi = std::min<int64_t>(s->tiles_per_item[prec], s->members.size() * ntiles / (4 * s->cus));
     if (tpi < 1)
         tpi = 1;
     const int64_t ipm = (ntiles + tpi - 1) / tpi;
