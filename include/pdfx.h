@@ -232,7 +232,9 @@ void pdfx_free_set(pdfx_set *s);
 
 /* out[m][p][r] = x f^{(m)}_{pids[r]}(x[p], q2[p]) for every member m.  x, q2
  * device FP64 [n_pts] shared by all members; out device [n_mem][n_pts][n_req]
- * FP64 or FP32 by precision.  Every member evaluates in one persistent launch
+ * FP64 or FP32 by precision.  Large calls with distinct pids that the set
+ * holds are evaluated by the routed kernel (see pdfx_get_launch), its launch
+ * preceded by one that cuts every member's grid.  Otherwise every member evaluates in one persistent launch
  * (after a one-thread kernel that resets its work-list cursor) that walks a
  * single list of (member, run of point tiles) items, the members of the
  * dearest node-width classes first; each item runs its member's class.  A
@@ -284,6 +286,10 @@ int pdfx_autotune(pdfx_grid *g, int prec, int32_t n_req, int64_t n_pts, const ch
 int pdfx_autotune_set(pdfx_set *s, int prec, int32_t n_req, int64_t n_pts, const char *cache_path);
 
 /* Current launch shape of a grid: workgroup size and points per thread.
+ * Large calls (from 400 thousand points on grids of up to 5000 knots, 200
+ * thousand on others) whose pids are distinct and held by the grid do not use
+ * it: they go to the routed kernel, which keeps the grid in LDS in pieces and has
+ * one shape, unless pdfx_set_launch has set a shape.
  * A default or tuned shape with ppt > 1 gives way to (512, 1) in a forward
  * call whose points fill fewer workgroups than half the compute units (e.g.
  * 1e5 points): smaller tiles keep more compute units busy.  A shape set by

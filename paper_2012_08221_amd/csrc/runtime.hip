@@ -12,6 +12,7 @@
 #include "../../include/pdfx.h"
 #include "pdfx_internal.h"
 #include "runtime_internal.h"
+#include "route_internal.h"
 #include "lumi_internal.h"
 #include "extrap_internal.h"
 #include "bwd_internal.h"
@@ -980,6 +981,57 @@ static bool plan_stages(XfxArgs &a, int G)
     return true;
 }
 
+// Teams of the routed kernel: one per XCD (workgroups go to the XCDs in turn).
+static void route_teams(int cus, RouteArgs *r)
+{
+    r->teams = cus % 8 == 0 ? 8 : 1;
+    r->team_size = cus / r->teams;
+}
+
+// Evaluates by the routed kernel if it takes the call: *done tells.
+static int run_route(const pdfx_grid *g, const XfxArgs &a, const void *xf_dev, int prec,
+                     hipStream_t s, bool *done)
+{
+    const bool f32 = prec == PDFX_F32S;
+    const int vs = f32 ? 4 : 8;
+    *done = false;
+    RouteArgs r{};
+    route_teams(g->cus, &r);
+    const RoutePlan plan = route_plan(a.nx, a.nq, a.ax.nbuckets, a.aq.nbuckets, a.n_u, vs,
+                                      a.as_out ? (a.nq + 2) * vs : 0);
+    if (plan.pieces < 1 || plan.pieces > std::min(kRouteMaxPieces, r.team_size))
+        return PDFX_OK;
+    r.one.ax = a.ax;
+    r.one.aq = a.aq;
+    r.one.nx = a.nx;
+    r.one.nq = a.nq;
+    r.one.slab64 = r.one.slab32 = a.slab_elems;
+    r.one.vals64 = r.one.vals32 = xf_dev ? xf_dev : g->vals[prec].ptr;
+    r.raw = xf_dev != nullptr;
+    r.ranges = r.n_units = r.teams;
+    r.range_pts = ((a.n + r.ranges - 1) / r.ranges + 63) / 64 * 64;
+    if (r.range_pts > (1 << 30))
+        return PDFX_OK;
+    r.ranges = r.n_units = (int)((a.n + r.range_pts - 1) / r.range_pts);
+    r.n_u = a.n_u;
+    for (int i = 0; i < kMaxReq; ++i)
+        r.urow[i] = a.urow[i];
+    r.x = a.x;
+    r.q = a.q;
+    r.q_is_q = a.q_is_q;
+    r.n = a.n;
+    r.out = a.out;
+    r.domain_mode = a.domain_mode;
+    r.dom_count = a.dom_count;
+    r.as_vals = a.as_vals;
+    r.as_out = a.as_out;
+    const hipError_t e = launch_route(r, f32, s);
+    if (e != hipSuccess)
+        return fail_hip(e, "xfx launch");
+    *done = true;
+    return PDFX_OK;
+}
+
 // Repack caller values (if any) and launch the forward kernel.  Shapes with
 // results held in registers (ppt > 0) use the flavour-group kernels when the
 // request's groups fit them: the double-buffered one when the grid fits its
@@ -993,6 +1045,16 @@ int run_xfx(const pdfx_grid *g, XfxArgs &a, const void *xf_dev, int prec, hipStr
     if (as_done)
         *as_done = false;
     LaunchShape ls = g->shape[prec];
+    if (!g->shape_pinned[prec] && a.n_u == a.n_req &&
+        a.n >= (g->dma_grid ? kRouteMinDma : kRouteMinOther)) {
+        bool done = false;
+        const int rc = run_route(g, a, xf_dev, prec, s, &done);
+        if (rc != PDFX_OK || done) {
+            if (as_done)
+                *as_done = a.as_out != nullptr;
+            return rc;
+        }
+    }
     if (!g->shape_pinned[prec] && ls.ppt > 1) {
         // a small call: (512, 1) gives twice or more the workgroups
         const int64_t tile = (int64_t)ls.block * ls.ppt;
@@ -1461,6 +1523,7 @@ int pdfx_load_set(const pdfx_grid_desc *members, int32_t n_mem, pdfx_set **out)
     hipError_t e;
     if ((e = s->mem_desc.upload(md.data(), md.size() * sizeof(MemberDev))) != hipSuccess ||
         (e = s->counter.upload(nullptr, 256)) != hipSuccess ||
+        (e = s->route_cuts.upload(nullptr, n_mem * sizeof(RouteCut))) != hipSuccess ||
         (e = s->dom_count.upload(nullptr, sizeof(unsigned long long))) != hipSuccess ||
         (e = s->call_count.upload(nullptr, sizeof(unsigned long long))) != hipSuccess) {
         delete s;
@@ -1521,7 +1584,8 @@ int pdfx_eval_set_xfx(const pdfx_set *s, int prec, const int32_t *pids, int32_t 
     // runs of tiles short enough to give every compute unit a few items
     // (101 members of 4000 points in runs of 4 tiles are 101 items: 167 us,
     // 62 us as 404)
-    int64_t tpi = std::min<int64_t>(s->tiles_per_item[prec], s->members.size() * ntiles / (4 * s->cus));
+    int64_t tpi =
+        std::min<int64_t>(s->tiles_per_item[prec], a.n_mem * ntiles / (4 * s->cus));
     if (tpi < 1)
         tpi = 1;
     const int64_t ipm = (ntiles + tpi - 1) / tpi;
@@ -1601,6 +1665,51 @@ int pdfx_eval_set_xfx(const pdfx_set *s, int prec, const int32_t *pids, int32_t 
         return err ? error_mode_end(s->call_count.ptr, (hipStream_t)stream, &s->host_count)
                    : PDFX_OK;
     };
+    RouteArgs r{};
+    route_teams(s->cus, &r);
+    bool route = fa.n_u == n_req && n_pts >= (dma ? kRouteMinSet : kRouteMinSetOdd) &&
+                 n_pts * a.n_mem >= (dma ? kRouteMinSetAll : kRouteMinSetOddAll);
+    for (int m = 0; m < a.n_mem && route; ++m) {
+        const pdfx_grid *g = s->members[m];
+        const RoutePlan p = route_plan(g->ax.n, g->aq.n, g->ax.nbuckets, g->aq.nbuckets, fa.n_u,
+                                       vs, 0);
+        route = p.pieces >= 1 && p.pieces <= std::min(kRouteMaxPieces, r.team_size);
+    }
+    if (route) {
+        // ranges of points per member, so that the units come out even among the teams
+        double best = 0.0;
+        for (int k = 1; k <= 2 * r.teams; ++k) {
+            const int rounds = (a.n_mem * k + r.teams - 1) / r.teams;
+            const double cost = rounds * ((double)n_pts / k + 4096.0 * r.team_size / 16);
+            if (k == 1 || cost < best) {
+                best = cost;
+                r.ranges = k;
+            }
+        }
+        r.range_pts = ((n_pts + r.ranges - 1) / r.ranges + 63) / 64 * 64;
+        if (r.range_pts > (1 << 30))
+            route = false;
+    }
+    if (route) {
+        r.ranges = (int)((n_pts + r.range_pts - 1) / r.range_pts);
+        r.n_units = a.n_mem * r.ranges;
+        r.mem = a.mem;
+        r.n_mem = a.n_mem;
+        r.cuts = (RouteCut *)s->route_cuts.ptr;
+        r.longest = std::max(s->max_nx, s->max_nq);
+        r.n_u = a.n_u;
+        for (int i = 0; i < kMaxReq; ++i)
+            r.urow[i] = a.urow[i];
+        r.x = x;
+        r.q = q2;
+        r.n = n_pts;
+        r.out = out;
+        r.domain_mode = domain_mode;
+        r.dom_count = a.dom_count;
+        if ((e = launch_route(r, f32, (hipStream_t)stream)) != hipSuccess)
+            return fail_hip(e, "set launch");
+        return done();
+    }
     if (dma) {
         if ((e = launch_set_dma(d, f32, ls, s->cus, (hipStream_t)stream)) != hipSuccess)
             return fail_hip(e, "set launch");

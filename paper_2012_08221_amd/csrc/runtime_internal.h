@@ -134,6 +134,7 @@ struct pdfx_set {
     std::vector<int32_t> pids;               // shared by every member
     pdfx::DeviceBuf mem_desc;                // MemberDev[n_mem]
     pdfx::DeviceBuf counter;                 // work-list cursor
+    pdfx::DeviceBuf route_cuts;              // RouteCut[n_mem], made by each routed call
     pdfx::DeviceBuf dom_count;
     pdfx::DeviceBuf call_count;              // PDFX_DOMAIN_ERROR calls, as for a grid
     mutable int64_t host_count = 0;

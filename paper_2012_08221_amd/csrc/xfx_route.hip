@@ -1,0 +1,944 @@
+// Routed forward kernel: batched x f(x, Q^2) of one grid or of every member
+// of a set, with the grid cut into pieces that stay in LDS.
+//
+// A grid's values for all requested partons (440 KB in FP64 for 11 x 100 x 50)
+// do not fit the 160 KB of a compute unit.  Instead of cycling flavour groups
+// through LDS for every tile of points, the grid is cut along one axis into
+// pieces (33 of 99 x intervals, with the 3 rows a window needs beyond them)
+// that hold every requested parton, and a workgroup keeps one piece for the
+// whole call.  It scans the points, takes those that fall into its piece (64
+// at a time, so that no lane idles) and writes their complete rows: nothing is
+// copied per tile, no barrier stands between the waves, and one wave's search
+// and logarithms run beside another's gathers.
+//
+// The workgroups of an XCD (by block index) form a team that works through a
+// range of points of one member; they are shared out among the pieces by the
+// share of the points in each, estimated from 1024 of them (the estimate only
+// decides who does what).  The pieces of a team sweep the range side by side,
+// so that the rows of neighbouring points, which share 128-byte lines, meet in
+// that XCD's L2.
+//
+// Same bins, weights and order of sums as the other forward kernels, so the
+// same bits.
+//
+// Bound by the LDS in FP64 (its pipe is busy for three quarters of the kernel,
+// two thirds of that in bank conflicts of the random 16-byte gathers) and by the
+// vector ALU and the LDS alike in FP32; rows that are finished by two
+// workgroups cost up to 60% more HBM writes than the rows' bytes.  10 million
+// points, 11 partons and alpha_s on 100 x 50 knots: 934 -> 497 us FP64 and 588 ->
+// 308 us FP32 against the double-buffered kernel's default shape; 3 million
+// points, 5 partons on 150 x 60 knots, continued outside: 345 -> 130 us; 101
+// members of 200003 points FP64: 4.37 -> 1.16 ms, of 1 million FP32: 5.97 -> 3.13.
+#include "route_internal.h"
+#include "set_internal.h"
+#include "xfx_fwd_impl.h"
+
+#include <type_traits>
+
+namespace pdfx {
+
+namespace {
+
+// Workgroup size by precision, one workgroup a compute unit: 16 waves of 128
+// registers in FP32; FP64, whose weights and gathers take twice the registers,
+// spills there and runs 12 waves (10 million points, 11 partons: 588 us against 601).
+template <typename V>
+constexpr int kRouteBlock = sizeof(V) == 8 ? 768 : 1024;
+constexpr int kRouteSamples = 1024;
+constexpr int kRouteScan = 4;      // tiles of 64 points whose coordinates are loaded at once
+
+// One axis of a piece in LDS: knots [0 .. cnt] of its cnt intervals, their
+// constants, and the bucket seeds of the whole axis (a: its first interval).
+struct PieceAxis {
+    const double *k;
+    const char *cst;
+    const uint16_t *seed;
+    int cnt, a, n, nb;
+    double lo, hi, ln_lo, inv_hb;
+};
+
+// Largest local interval i with k[i] <= v, kept in the piece: the bucket's seed
+// and the two knots after it settle nearly every point at once; the others walk.
+__device__ __forceinline__ int piece_bin(const PieceAxis &p, double v, double lnv)
+{
+    const double fb = (lnv - p.ln_lo) * p.inv_hb;
+    const int b = fb <= 0.0 ? 0 : (fb >= (double)(p.nb - 1) ? p.nb - 1 : (int)fb);
+    const int top = p.cnt - 1;
+    int i = (int)p.seed[b] - p.a;
+    i = min(max(i, 0), top);
+    const double k0 = p.k[i], k1 = p.k[i + 1], k2 = p.k[min(i + 2, p.cnt)];
+    const bool up1 = i < top && k1 <= v, up2 = up1 && i + 1 < top && k2 <= v;
+    i += (int)up1 + (int)up2;
+    if (up2 || k0 > v) {
+        while (i < top && p.k[i + 1] <= v)
+            ++i;
+        while (i > 0 && p.k[i] > v)
+            --i;
+    }
+    return i;
+}
+
+// Folded weights of local interval i from its constants: z and 1/d (FP64),
+// then pl, pr (FP64) or pl, pl-ql, qr-pr, pr (FP32); ql and qr are 1/2 inside
+// the subgrid and 1 at its ends, where pl or pr is 0.
+template <typename W>
+__device__ __forceinline__ void piece_weights(const PieceAxis &p, int i, double lnv, W w[4]);
+template <>
+__device__ __forceinline__ void piece_weights<double>(const PieceAxis &p, int i, double lnv,
+                                                      double w[4])
+{
+    const double2 c = *reinterpret_cast<const double2 *>(p.cst + i * 32);
+    const double2 e = *reinterpret_cast<const double2 *>(p.cst + i * 32 + 16);
+    const double t = (lnv - c.x) * c.y;
+    const double ql = e.x != 0.0 ? 0.5 : 1.0, qr = e.y != 0.0 ? 0.5 : 1.0;
+    fwd::fold<double>(t, e.x, e.x - ql, ql, qr, qr - e.y, e.y, w);
+}
+template <>
+__device__ __forceinline__ void piece_weights<float>(const PieceAxis &p, int i, double lnv,
+                                                     float w[4])
+{
+    const double2 c = *reinterpret_cast<const double2 *>(p.cst + i * 32);
+    const float4 e = *reinterpret_cast<const float4 *>(p.cst + i * 32 + 16);
+    const float t = (float)((lnv - c.x) * c.y);
+    const float ql = e.x != 0.f ? 0.5f : 1.f, qr = e.w != 0.f ? 0.5f : 1.f;
+    fwd::fold<float>(t, e.x, e.y, ql, qr, e.z, e.w, w);
+}
+
+// Window of global interval i on an axis of n knots (as the double-buffered
+// kernel): its first knot, the weights moved along at the ends.
+template <typename W>
+__device__ __forceinline__ int window4(int i, int n, W w[4])
+{
+    int st = i - 1;
+    if (st < 0) {
+        st = 0;
+        w[0] = w[1];
+        w[1] = w[2];
+        w[2] = w[3];
+        w[3] = W(0);
+    } else if (st > n - 4) {
+        st = n - 4;
+        w[3] = w[2];
+        w[2] = w[1];
+        w[1] = w[0];
+        w[0] = W(0);
+    }
+    return st;
+}
+
+// K values of V side by side in LDS.
+template <typename V, int K>
+__device__ __forceinline__ void lds_values(const char *p, V v[K])
+{
+    if constexpr (sizeof(V) * K == 16) {
+        const uint4 d = *reinterpret_cast<const uint4 *>(p);
+        __builtin_memcpy(v, &d, 16);
+    } else if constexpr (sizeof(V) * K == 8) {
+        const uint2 d = *reinterpret_cast<const uint2 *>(p);
+        __builtin_memcpy(v, &d, 8);
+    } else {
+        v[0] = *reinterpret_cast<const V *>(p);
+    }
+}
+
+// 16-tap stencil of the K rows of one plane at node address p (bytes), rows
+// row_bytes apart.
+template <typename V, int K>
+__device__ __forceinline__ void plane_stencil(const char *p, int row_bytes, const V wx[4],
+                                              const V wq[4], V acc[K])
+{
+    constexpr int NB = (int)sizeof(V) * K;
+#pragma unroll
+    for (int jx = 0; jx < 4; ++jx) {
+        V r[K];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            V v[K];
+            lds_values<V, K>(p + jx * row_bytes + k * NB, v);
+#pragma unroll
+            for (int g = 0; g < K; ++g)
+                r[g] = (k == 0) ? wq[0] * v[g] : fma(wq[k], v[g], r[g]);
+        }
+#pragma unroll
+        for (int g = 0; g < K; ++g)
+            acc[g] = (jx == 0) ? wx[0] * r[g] : fma(wx[jx], r[g], acc[g]);
+        // eight reads in flight a wave: with 16 waves that fills the LDS pipe, and
+        // sixteen would not fit the 128 registers
+        if (jx == 1)
+            asm volatile("" ::: "memory");
+    }
+}
+
+// The lane's register of another lane of its quad.
+template <int CTRL>
+__device__ __forceinline__ uint32_t quad_lane(uint32_t v)
+{
+    return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, 0xf, true);
+}
+
+// Exchanges between lanes l and l ^ D (D = 1, 2) the 16-byte pieces c0 of the
+// lanes with that bit set against the c1 of the others.
+template <int D>
+__device__ __forceinline__ void swap_pieces(int lane, uint4 &c0, uint4 &c1)
+{
+    constexpr int CTRL = D == 1 ? 0xB1 : 0x4E;   // quad_perm [1,0,3,2], [2,3,0,1]
+    const bool up = lane & D;
+    auto one = [&](uint32_t &a, uint32_t &b) {
+        const uint32_t fa = quad_lane<CTRL>(a), fb = quad_lane<CTRL>(b);
+        a = up ? fb : a;
+        b = up ? b : fa;
+    };
+    one(c0.x, c1.x);
+    one(c0.y, c1.y);
+    one(c0.z, c1.z);
+    one(c0.w, c1.w);
+}
+
+template <int K, typename V>
+__device__ __forceinline__ void store_values(V *dst, const V v[K])
+{
+    if constexpr (K == 4) {
+        typedef V vec __attribute__((ext_vector_type(4), aligned(sizeof(V))));
+        *reinterpret_cast<vec *>(dst) = vec{v[0], v[1], v[2], v[3]};
+    } else if constexpr (K == 3) {
+        typedef V vec __attribute__((ext_vector_type(3), aligned(sizeof(V))));
+        *reinterpret_cast<vec *>(dst) = vec{v[0], v[1], v[2]};
+    } else if constexpr (K == 2) {
+        typedef V vec __attribute__((ext_vector_type(2), aligned(sizeof(V))));
+        *reinterpret_cast<vec *>(dst) = vec{v[0], v[1]};
+    } else {
+#pragma unroll
+        for (int g = 0; g < K; ++g)
+            dst[g] = v[g];
+    }
+}
+
+// Places one axis part (intervals a .. a + cnt - 1) in LDS at *off.
+__device__ __forceinline__ PieceAxis place_axis(char *sm, int &off, const AxisDev &ax, int a,
+                                                int cnt)
+{
+    PieceAxis p;
+    p.k = reinterpret_cast<const double *>(sm + off);
+    off += route_round16((cnt + 1) * 8);
+    p.cst = sm + off;
+    off += cnt * 32;
+    p.seed = reinterpret_cast<const uint16_t *>(sm + off);
+    off += route_round16(ax.nbuckets * 2);
+    p.cnt = cnt;
+    p.a = a;
+    p.n = ax.n;
+    p.nb = ax.nbuckets;
+    p.lo = ax.lo;
+    p.hi = ax.hi;
+    p.ln_lo = ax.ln_lo;
+    p.inv_hb = ax.inv_hb;
+    return p;
+}
+
+// Copies the tables of both axis parts into LDS; all loads of a thread are
+// issued before its first write.
+template <bool F32, int BLOCK>
+__device__ __forceinline__ void load_axes(const PieceAxis (&p)[2], const AxisDev *const (&ax)[2])
+{
+    const int most = max(max(p[0].cnt + 1, p[0].nb / 2), max(p[1].cnt + 1, p[1].nb / 2));
+    for (int i = threadIdx.x; i < most; i += BLOCK) {
+        double k[2], z[2][2], c64[2][2];
+        float c32[2][4];
+        unsigned int sd[2];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int a = p[s].a, ik = min(i, p[s].cnt), ic = min(i, p[s].cnt - 1);
+            gptr<double> r64 = (gptr<double>)(ax[s]->rec64 + a + ic);
+            k[s] = ((gptr<double>)ax[s]->knots)[a + ik];
+            z[s][0] = r64[0];
+            z[s][1] = r64[1];
+            if constexpr (F32) {
+                gptr<float> r32 = (gptr<float>)(ax[s]->rec32 + a + ic);
+                c32[s][0] = r32[2];
+                c32[s][1] = r32[3];
+                c32[s][2] = r32[6];
+                c32[s][3] = r32[7];
+            } else {
+                c64[s][0] = r64[2];
+                c64[s][1] = r64[7];
+            }
+            sd[s] = ((gptr<unsigned int>)ax[s]->seed)[min(i, p[s].nb / 2 - 1)];   // nb % 4 == 0
+        }
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            double *d = reinterpret_cast<double *>(const_cast<char *>(p[s].cst) + i * 32);
+            if (i <= p[s].cnt)
+                const_cast<double *>(p[s].k)[i] = k[s];
+            if (i < p[s].cnt) {
+                d[0] = z[s][0];
+                d[1] = z[s][1];
+                if constexpr (F32) {
+                    float *f = reinterpret_cast<float *>(d + 2);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        f[j] = c32[s][j];
+                } else {
+                    d[2] = c64[s][0];
+                    d[3] = c64[s][1];
+                }
+            }
+            if (i < p[s].nb / 2)
+                reinterpret_cast<unsigned int *>(const_cast<uint16_t *>(p[s].seed))[i] = sd[s];
+        }
+    }
+}
+
+// Shares team_size workgroups among the pieces by weight w (one lane per
+// piece, pieces <= team_size): at least one each, the others to the piece with
+// the largest weight per workgroup.  Returns the lane's number.
+__device__ __forceinline__ int share_out(float w, int pieces, int team_size)
+{
+    const int lane = threadIdx.x & 63;
+    float sum = lane < pieces ? w : 0.f;
+    for (int d = 32; d; d >>= 1)
+        sum += __shfl_xor(sum, d);
+    int mine = lane < pieces ? (int)(w / sum * (float)team_size) : 0;
+    if (lane < pieces && mine < 1)
+        mine = 1;
+    int total = mine;
+    for (int d = 32; d; d >>= 1)
+        total += __shfl_xor(total, d);
+    // too many (pieces raised to one): from the lightest load; too few: to the heaviest
+    while (total != team_size) {
+        const bool more = total < team_size;
+        float key = -1.f;
+        if (lane < pieces)
+            key = more ? w / (float)mine : (mine > 1 ? 1.f / (w / (float)(mine - 1) + 1e-30f) : -1.f);
+        int at = lane;
+        for (int d = 32; d; d >>= 1) {
+            const float k2 = __shfl_xor(key, d);
+            const int a2 = __shfl_xor(at, d);
+            if (k2 > key || (k2 == key && a2 < at)) {
+                key = k2;
+                at = a2;
+            }
+        }
+        if (lane == at)
+            mine += more ? 1 : -1;
+        total += more ? 1 : -1;
+    }
+    return mine;
+}
+
+// Makes the cut of an axis of ns knots (ks) for pieces of at most `most`
+// intervals.  knots, cum: LDS for ns doubles and ns ints.  Every workgroup of
+// the team makes the same one from the same samples.
+template <int BLOCK>
+__device__ __forceinline__ void make_cut(RouteCut *rc, double *knots, int *cum, gptr<double> ks,
+                                         int ns, int most, const double *sp, bool square,
+                                         int64_t n, int team_size)
+{
+    constexpr int S = kRouteSamples, PER = (S + BLOCK - 1) / BLOCK;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));   // nothing of this is kept in registers beyond it
+    const int lane = tid & 63;
+    const int ni = ns - 1;
+    double v[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k)
+        v[k] = sp[(int64_t)min(k * BLOCK + tid, S - 1) * n / S];
+    for (int i = tid; i < ns; i += BLOCK) {
+        knots[i] = ks[i];
+        cum[i] = 0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        if (k * BLOCK + tid >= S)
+            break;
+        const double u = square ? v[k] * v[k] : v[k];
+        int lo = 0, hi = ni;              // interval in [lo, hi)
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (u >= knots[mid])
+                lo = mid;
+            else
+                hi = mid;
+        }
+        atomicAdd(&cum[lo], 1);
+    }
+    __syncthreads();
+    if (tid < 64) {
+        // running sums: cum[i] = samples in intervals [0, i]
+        const int per = (ni + 63) / 64;
+        int own = 0;
+        for (int i = lane * per; i < (lane + 1) * per && i < ni; ++i) {
+            own += cum[i];
+            cum[i] = own;
+        }
+        int incl = own;
+        for (int d = 1; d < 64; d <<= 1) {
+            const int o = __shfl_up(incl, d);
+            incl += lane >= d ? o : 0;
+        }
+        for (int i = lane * per; i < (lane + 1) * per && i < ni; ++i)
+            cum[i] += incl - own;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        // first interval with more than c samples up to and in it, or ni
+        auto reach = [&](int c) {
+            int lo = 0, hi = ni;
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (cum[mid] > c)
+                    hi = mid;
+                else
+                    lo = mid + 1;
+            }
+            return lo;
+        };
+        int a = reach(0), b = reach(S - 1) + 1;
+        const int pieces = (b - a + most - 1) / most;
+        // room left in the pieces goes to the intervals beyond, half to either side
+        int spare = pieces * most - (b - a);
+        const int down = min(a, max(spare / 2, spare - (ni - b)));
+        a -= down;
+        spare -= down;
+        b += min(ni - b, spare);
+        const int below = a > 0 ? cum[a - 1] : 0, inside = cum[b - 1] - below;
+        // equal shares of the samples, as far as `most` allows
+        int want = reach(below + (int)((int64_t)inside * lane / pieces) - 1) + 1;
+        int cut = a;
+        for (int k = 1; k < pieces; ++k) {
+            const int prev = __shfl(cut, k - 1), w = __shfl(want, k);
+            int c = max(w, max(prev + 1, b - (pieces - k) * most));
+            c = min(c, min(prev + most, b - (pieces - k)));
+            if (lane == k)
+                cut = c;
+        }
+        if (lane >= pieces)
+            cut = b;
+        const int next = __shfl(cut, lane < 63 ? lane + 1 : 63);
+        // a scan costs about 1/32 of an evaluation per point and piece
+        const int held = lane < pieces ? cum[next - 1] - (cut > 0 ? cum[cut - 1] : 0) : 0;
+        const int width = share_out((float)held + (float)S * (1.f / 32.f), pieces, team_size);
+        if (lane < pieces) {
+            rc->cut[lane] = cut;
+            rc->width[lane] = width;
+        }
+        if (lane == 0) {
+            rc->pieces = pieces;
+            rc->cut[pieces] = b;
+        }
+    }
+    __syncthreads();
+}
+
+// Member m, read through the scalar cache (the table is constant).
+typedef const __attribute__((address_space(4))) uint32_t *cptr32;
+__device__ __forceinline__ MemberDev member(const RouteArgs &a, int m)
+{
+    MemberDev md = a.one;
+    if (a.mem) {
+        cptr32 g = (cptr32)(uintptr_t)(a.mem + m);
+        uint32_t w[sizeof(MemberDev) / 4];
+#pragma unroll
+        for (int i = 0; i < (int)(sizeof(MemberDev) / 4); ++i)
+            w[i] = g[i];
+        __builtin_memcpy(&md, w, sizeof(MemberDev));
+    }
+    return md;
+}
+
+// Bin and folded weights from the tables in global memory, for the points
+// outside every piece.
+template <typename W>
+__device__ __forceinline__ int far_weights(const AxisDev &ax, double v, double lnv, W w[4])
+{
+    const double fb = (lnv - ax.ln_lo) * ax.inv_hb;
+    const int b = fb <= 0.0 ? 0 : (fb >= (double)(ax.nbuckets - 1) ? ax.nbuckets - 1 : (int)fb);
+    gptr<double> k = (gptr<double>)ax.knots;
+    int i = ((gptr<uint16_t>)ax.seed)[b];
+    while (i < ax.n - 2 && k[i + 1] <= v)
+        ++i;
+    while (i > 0 && k[i] > v)
+        --i;
+    gptr<double> d = (gptr<double>)(ax.rec64 + i);
+    if constexpr (sizeof(W) == 8) {
+        const double t = (lnv - d[0]) * d[1];
+        fwd::fold<double>(t, d[2], d[3], d[4], d[5], d[6], d[7], w);
+    } else {
+        gptr<float> f = (gptr<float>)(ax.rec32 + i);
+        const float t = (float)((lnv - d[0]) * d[1]);
+        fwd::fold<float>(t, f[2], f[3], f[4], f[5], f[6], f[7], w);
+    }
+    return i;
+}
+
+// The lane, recomputed where it is used: what is derived from it is then not
+// kept in registers across the loops, which have none to spare.
+__device__ __forceinline__ int fresh_lane()
+{
+    int l;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+    return l;
+}
+
+template <typename V, bool AS>
+__global__ __launch_bounds__(kRouteBlock<V>) void xfx_route_kernel(const RouteArgs a)
+{
+    constexpr int BLOCK = kRouteBlock<V>, WAVES = BLOCK / 64;
+    constexpr bool F32 = sizeof(V) == 4;
+    constexpr int G = 16 / (int)sizeof(V);
+    extern __shared__ uint4 smem4[];
+    char *sm = reinterpret_cast<char *>(smem4);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int team = blockIdx.x % a.teams, place = blockIdx.x / a.teams;
+    const int n_u = a.n_u;
+    const int full = n_u / G;                                       // 16-byte planes
+    const int tail = route_tail_bytes(n_u, (int)sizeof(V));         // bytes of the last plane
+
+    for (int unit = team; unit < a.n_units; unit += a.teams) {
+        const int m = unit / a.ranges;
+        const MemberDev md = member(a, m);
+        const int nx = md.nx, nq = md.nq;
+        const int64_t p0 = (int64_t)(unit - m * a.ranges) * a.range_pts;
+        const int64_t left = a.n - p0;
+        const int npts = (int)(left < a.range_pts ? left : a.range_pts);
+        const RoutePlan plan = route_plan(nx, nq, md.ax.nbuckets, md.aq.nbuckets, n_u,
+                                          (int)sizeof(V), AS ? (nq + 2) * (int)sizeof(V) : 0);
+        const bool by_q = plan.split != 0;
+        const int ns = by_q ? nq : nx;                              // knots of the split axis
+        gptr<double> ks = (gptr<double>)(by_q ? md.aq.knots : md.ax.knots);
+        const double *sp = by_q ? a.q : a.x;
+        const bool square = by_q && a.q_is_q;
+
+        // this workgroup's piece [ia, ib), and which of the `width` workgroups
+        // that sweep it this one is
+        int ia = 0, ib = ns - 1, piece = 0, part = place, width = a.team_size;
+        int cut_lo = 0, cut_hi = ns - 1;                            // intervals held by any piece
+        __syncthreads();   // the previous unit has left LDS
+        if (plan.pieces > 1) {
+            RouteCut *rc = reinterpret_cast<RouteCut *>(sm);
+            double *kn = reinterpret_cast<double *>(sm + route_round16(sizeof(RouteCut)));
+            if (a.cuts) {
+                // made by route_cut_kernel
+                gptr<int> g = (gptr<int>)(a.cuts + m);
+                if (tid < (int)(sizeof(RouteCut) / 4))
+                    reinterpret_cast<int *>(rc)[tid] = g[tid];
+                __syncthreads();
+            } else {
+                make_cut<BLOCK>(rc, kn, reinterpret_cast<int *>(kn + ns), ks, ns, plan.most, sp, square,
+                         a.n, a.team_size);
+            }
+            while (part >= rc->width[piece]) {
+                part -= rc->width[piece];
+                ++piece;
+            }
+            width = __builtin_amdgcn_readfirstlane(rc->width[piece]);
+            ia = __builtin_amdgcn_readfirstlane(rc->cut[piece]);
+            ib = __builtin_amdgcn_readfirstlane(rc->cut[piece + 1]);
+            cut_lo = __builtin_amdgcn_readfirstlane(rc->cut[0]);
+            cut_hi = __builtin_amdgcn_readfirstlane(rc->cut[rc->pieces]);
+            piece = __builtin_amdgcn_readfirstlane(piece);
+            part = __builtin_amdgcn_readfirstlane(part);
+            __syncthreads();   // read before the values are written over it
+        }
+        // points of the piece: s_lo <= v < s_hi, without a bound at an end of
+        // the axis (the lower end's piece takes NaN); piece 0 also takes the
+        // points outside every piece
+        const bool first = ia == 0, last = ib == ns - 1;
+        const double s_lo = ks[ia], s_hi = last ? __builtin_inf() : ks[ib];
+        const bool far_lo = piece == 0 && cut_lo > 0, far_hi = piece == 0 && cut_hi < ns - 1;
+        const bool far_any = far_lo || far_hi;
+        const double f_hi = far_hi ? ks[cut_hi] : __builtin_inf();
+
+        // knots [w0, w0 + wn) of the split axis are in LDS
+        auto start = [&](int i) { return i - 1 < 0 ? 0 : i - 1 > ns - 4 ? ns - 4 : i - 1; };
+        const int w0 = start(ia), wn = start(ib - 1) + 4 - w0;
+        const int x0 = by_q ? 0 : w0, xn = by_q ? nx : wn;
+        const int q0 = by_q ? w0 : 0, qn = by_q ? wn : nq;
+        const int nodes = xn * qn;
+        const int plane = nodes * 16;                               // bytes of a full plane
+
+        // values: wave by (row, x), lanes over Q^2
+        const V *const src = reinterpret_cast<const V *>(F32 ? md.vals32 : md.vals64);
+        const int rs = a.raw ? nq : nq + 2;
+        const size_t fs = a.raw ? (size_t)nx * nq : (size_t)(F32 ? md.slab32 : md.slab64);
+        const size_t o0 = a.raw ? 0 : (size_t)rs + 1;
+        // (H rows of four x values at once, so that as many loads are in flight)
+        constexpr int H = F32 ? 4 : 2;
+        const int urow = lane < n_u ? a.urow[lane] : 0;
+        for (int u = 0; u < n_u; u += H) {
+            gptr<V> g[H];
+            int dst[H], step[H];
+#pragma unroll
+            for (int h = 0; h < H; ++h) {
+                const int uh = min(u + h, n_u - 1);
+                g[h] = (gptr<V>)(src + (size_t)__builtin_amdgcn_readlane(urow, uh) * fs + o0 +
+                                 (size_t)x0 * rs + q0);
+                dst[h] = (uh / G) * plane + (uh % G) * (int)sizeof(V);
+                step[h] = uh >= full * G ? tail : 16;
+            }
+            for (int i0 = wave; i0 < xn; i0 += 4 * WAVES)
+                for (int k = lane; k < qn; k += 64) {
+                    V v[H][4];
+#pragma unroll
+                    for (int h = 0; h < H; ++h)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            const int i = i0 + j * WAVES;
+                            v[h][j] = g[h][(i < xn ? i : i0) * rs + k];
+                        }
+#pragma unroll
+                    for (int h = 0; h < H; ++h)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            const int i = i0 + j * WAVES;
+                            if (i < xn)
+                                *reinterpret_cast<V *>(sm + dst[h] + (i * qn + k) * step[h]) =
+                                    v[h][j];
+                        }
+                }
+        }
+        int off = route_round16(full * plane + nodes * tail);
+        const PieceAxis px = place_axis(sm, off, md.ax, by_q ? 0 : ia, by_q ? nx - 1 : ib - ia);
+        const PieceAxis pq = place_axis(sm, off, md.aq, by_q ? ia : 0, by_q ? ib - ia : nq - 1);
+        {
+            const PieceAxis both[2] = {px, pq};
+            const AxisDev *const axes[2] = {&md.ax, &md.aq};
+            load_axes<F32, BLOCK>(both, axes);
+        }
+        const V *asv = reinterpret_cast<const V *>(sm + off) + 1;   // padded by one on each side
+        if constexpr (AS) {
+            gptr<V> gv = (gptr<V>)a.as_vals;
+            for (int i = tid; i < nq + 2; i += BLOCK)
+                reinterpret_cast<V *>(sm + off)[i] = gv[i];
+        }
+        __syncthreads();
+
+        V *const out = reinterpret_cast<V *>(a.out) + ((int64_t)m * a.n + p0) * n_u;
+        const double *const xp = a.x + p0, *const qp = a.q + p0, *const spp = sp + p0;
+        const int ntile = (npts + 63) / 64;
+        const int stride = width * WAVES;
+
+        // Domain rule for the point (x, Q^2); x f is defined (ok), alpha_s is (q_ok).
+        auto admit = [&](double &xv, double &qv, bool &q_ok) {
+            const bool x_in = xv >= px.lo && xv <= px.hi;   // false for NaN
+            const bool q_in = qv >= pq.lo && qv <= pq.hi;
+            bool ok = x_in && q_in;
+            q_ok = true;
+            if (!ok) {
+                const bool x_nan = xv != xv, q_nan = qv != qv;
+                if (a.domain_mode == 1) {
+                    ok = !x_nan && !q_nan;
+                    q_ok = !q_nan;
+                    xv = x_nan ? px.lo : fmin(fmax(xv, px.lo), px.hi);
+                    qv = q_nan ? pq.lo : fmin(fmax(qv, pq.lo), pq.hi);
+                } else {
+                    q_ok = q_in;
+                    xv = x_in ? xv : px.lo;
+                    qv = q_in ? qv : pq.lo;
+                }
+            }
+            return ok;
+        };
+        auto alphas = [&](int rel, bool live, bool q_ok, int sq, const V wq[4]) {
+            const V *av = asv + sq;
+            V s = wq[0] * av[0];
+            s = fma(wq[1], av[1], s);
+            s = fma(wq[2], av[2], s);
+            s = fma(wq[3], av[3], s);
+            if (live)
+                reinterpret_cast<V *>(a.as_out)[p0 + rel] = q_ok ? s : fwd::quiet_nan<V>();
+        };
+
+        // Tiles of 64 points t, t + stride, ... of this wave, scanned kRouteScan at
+        // a time; bit k of `bits` tells that the lane's point of the k-th tile is
+        // the piece's.  The next tiles' coordinates are loaded ahead (vn, `raw`
+        // until they are made into bits).
+        const int t_first = part * WAVES + wave;
+        int t_load = t_first, t_use = t_first, held = 0;
+        double vn[kRouteScan];
+        unsigned int bits = 0, bits_next = 0;
+        bool raw = false, far_seen = false;
+        auto load_tiles = [&]() {
+            const int lane = fresh_lane();
+#pragma unroll
+            for (int k = 0; k < kRouteScan; ++k) {
+                const int rel = (t_load + k * stride) * 64 + lane;
+                vn[k] = spp[rel < npts ? rel : npts - 1];
+            }
+            raw = true;
+        };
+        auto is_far = [&](double v) { return (far_lo && !(v >= s_lo)) || (far_hi && v >= f_hi); };
+        auto make_bits = [&]() {
+            const int lane = fresh_lane();
+            bits_next = 0;
+#pragma unroll
+            for (int k = 0; k < kRouteScan; ++k) {
+                const int rel = (t_load + k * stride) * 64 + lane;
+                double v = vn[k];
+                if (square)
+                    v = v * v;
+                if (rel < npts && (first || v >= s_lo) && !(v >= s_hi))
+                    bits_next |= 1u << k;
+                if (far_any)
+                    far_seen = far_seen || is_far(v);
+            }
+            raw = false;
+        };
+        // The points waiting: lanes [0, n_wait) of `wait`, and past 64 those of `over`.
+        int n_wait = 0, wait = 0, over = 0;
+        // The next batch of 64; its coordinates are loaded at once.
+        int b_n = 0, b_rel = 0;
+        double b_x = 0.0, b_q = 0.0;
+        auto next_batch = [&]() {
+            const int lane = fresh_lane();
+            while (n_wait < 64 && (held > 0 || t_load < ntile)) {
+                if (held == 0) {
+                    if (raw)
+                        make_bits();
+                    bits = bits_next;
+                    t_use = t_load;
+                    held = kRouteScan;
+                    t_load += kRouteScan * stride;
+                    if (t_load < ntile)
+                        load_tiles();
+                }
+                const bool sel = bits & 1u;
+                const unsigned long long mask = __ballot(sel);
+                if (mask != 0ull) {
+                    // the tile's points go to the lanes after those waiting, the
+                    // other lanes fill up
+                    const int hits = __popcll(mask);
+                    const int before = __builtin_amdgcn_mbcnt_hi(
+                        (unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
+                    const int dest = n_wait + (sel ? before : hits + lane - before);
+                    over = __builtin_amdgcn_ds_permute((dest & 63) * 4, t_use * 64 + lane);
+                    wait = lane < n_wait ? wait : over;
+                    n_wait += hits;
+                }
+                bits >>= 1;
+                t_use += stride;
+                --held;
+            }
+            b_n = n_wait;
+            b_rel = lane < n_wait ? wait : __builtin_amdgcn_readfirstlane(wait);
+            wait = over;
+            n_wait = n_wait > 64 ? n_wait - 64 : 0;
+            b_x = xp[b_rel];
+            b_q = qp[b_rel];
+        };
+        if (t_load < ntile)
+            load_tiles();
+        next_batch();
+        while (b_n > 0) {
+            const int lane = fresh_lane();
+            const int n_now = b_n, rel = b_rel;
+            const bool live = lane < n_now;
+            double xv = b_x, qv = b_q;
+            next_batch();
+            if (a.q_is_q)
+                qv = qv * qv;
+            bool q_ok;
+            const bool ok = admit(xv, qv, q_ok);
+            fwd::count_flagged(live && !ok, a.dom_count);
+            if constexpr (AS)
+                fwd::count_flagged(live && !q_ok, a.dom_count);
+            const double lnx = log(xv), lnq = log(qv);
+            V wx[4], wq[4];
+            const int ix = piece_bin(px, xv, lnx);
+            const int kq = piece_bin(pq, qv, lnq);
+            piece_weights<V>(px, ix, lnx, wx);
+            piece_weights<V>(pq, kq, lnq, wq);
+            const int sx = window4(ix + px.a, nx, wx);
+            const int sq = window4(kq + pq.a, nq, wq);
+            // a point outside the grid: NaN weights make all its values NaN
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                wx[k] = ok ? wx[k] : fwd::quiet_nan<V>();
+            // The loads ahead are waited for here, before this batch's stores:
+            // memory operations complete in order, and a wait for a load that was
+            // issued after them would wait for the stores as well.
+            asm volatile("" : "+v"(b_x), "+v"(b_q));
+            if (raw)
+                make_bits();
+            if constexpr (AS)
+                alphas(rel, live, q_ok, sq, wq);
+            const int node = (sx - x0) * qn + (sq - q0);
+            const char *p = sm + node * 16;
+            // C planes side by side: each row's C * 16 bytes leave from C
+            // neighbouring lanes in one store, a quarter (C = 4) of the line
+            // requests of a store of 16 bytes per lane and row
+            auto planes = [&](int g, auto cc) {
+                constexpr int C = decltype(cc)::value;
+                uint4 c[C];
+#pragma unroll
+                for (int j = 0; j < C; ++j, p += plane) {
+                    V acc[G];
+                    plane_stencil<V, G>(p, qn * 16, wx, wq, acc);
+                    __builtin_memcpy(&c[j], acc, 16);
+                    asm volatile("" ::: "memory");
+                }
+                if constexpr (C >= 2)
+#pragma unroll
+                    for (int j = 0; j < C; j += 2)
+                        swap_pieces<1>(lane, c[j], c[j + 1]);
+                if constexpr (C == 4) {
+                    swap_pieces<2>(lane, c[0], c[2]);
+                    swap_pieces<2>(lane, c[1], c[3]);
+                }
+#pragma unroll
+                for (int j = 0; j < C; ++j) {
+                    // row of the j-th of the C lanes, piece of this lane
+                    int rj = rel;
+                    if constexpr (C == 2)
+                        rj = j ? quad_lane<0xF5>(rel) : quad_lane<0xA0>(rel);
+                    else if constexpr (C == 4)
+                        rj = j == 0   ? quad_lane<0x00>(rel)
+                             : j == 1 ? quad_lane<0x55>(rel)
+                             : j == 2 ? quad_lane<0xAA>(rel)
+                                      : quad_lane<0xFF>(rel);
+                    V v[G];
+                    __builtin_memcpy(v, &c[j], 16);
+                    if ((lane & ~(C - 1)) + j < n_now)
+                        store_values<G>(out + (int64_t)rj * n_u + (g + (lane & (C - 1))) * G, v);
+                }
+            };
+            int g = 0;
+            for (; g + 4 <= full; g += 4)
+                planes(g, std::integral_constant<int, 4>{});
+            if (g + 2 <= full) {
+                planes(g, std::integral_constant<int, 2>{});
+                g += 2;
+            }
+            if (g < full)
+                planes(g, std::integral_constant<int, 1>{});
+            if (tail) {
+                const int u0 = full * G, left = n_u - u0;
+                V *const row = out + (int64_t)rel * n_u + u0;
+                V acc[G];
+                p = sm + full * plane + node * tail;
+                if (left == 1) {
+                    plane_stencil<V, 1>(p, qn * tail, wx, wq, acc);
+                    if (live)
+                        store_values<1>(row, acc);
+                } else if constexpr (F32) {
+                    if (left == 2) {
+                        plane_stencil<V, 2>(p, qn * tail, wx, wq, acc);
+                        if (live)
+                            store_values<2>(row, acc);
+                    } else {
+                        plane_stencil<V, 4>(p, qn * tail, wx, wq, acc);
+                        if (live)
+                            store_values<3>(row, acc);
+                    }
+                }
+            }
+        }
+
+        // Points outside every piece (the sample held none): again over the
+        // tiles of this wave, straight from the values in global memory.
+        if (far_any && __ballot(far_seen) != 0ull) {
+            int m_far = m;
+            asm volatile("" : "+s"(m_far));   // read again: its tables are not kept till here
+            const MemberDev md = member(a, m_far);
+            const int nx = md.nx, nq = md.nq;
+            const V *const src = reinterpret_cast<const V *>(F32 ? md.vals32 : md.vals64);
+            const int rs = a.raw ? nq : nq + 2;
+            const size_t fs = a.raw ? (size_t)nx * nq : (size_t)(F32 ? md.slab32 : md.slab64);
+            const size_t o0 = a.raw ? 0 : (size_t)rs + 1;
+            for (int t = t_first; t < ntile; t += stride) {
+                const int rel = t * 64 + lane;
+                double v = spp[rel < npts ? rel : npts - 1];
+                if (square)
+                    v = v * v;
+                if (rel >= npts || !is_far(v))
+                    continue;
+                double xv = xp[rel], qv = qp[rel];
+                if (a.q_is_q)
+                    qv = qv * qv;
+                bool q_ok;
+                const bool ok = admit(xv, qv, q_ok);
+                const int flags = (ok ? 0 : 1) + (AS && !q_ok ? 1 : 0);
+                if (flags)   // only some lanes are here
+                    atomicAdd(a.dom_count, (unsigned long long)flags);
+                const double lnx = log(xv), lnq = log(qv);
+                V wx[4], wq[4];
+                const int ix = far_weights<V>(md.ax, xv, lnx, wx);
+                const int kq = far_weights<V>(md.aq, qv, lnq, wq);
+                const int sx = window4(ix, nx, wx);
+                const int sq = window4(kq, nq, wq);
+                if constexpr (AS)
+                    alphas(rel, true, q_ok, sq, wq);
+                gptr<V> g0 = (gptr<V>)(src + o0 + (size_t)sx * rs + sq);
+                for (int u = 0; u < n_u; ++u) {
+                    gptr<V> g = g0 + (size_t)a.urow[u] * fs;
+                    V acc = V(0);
+#pragma unroll
+                    for (int jx = 0; jx < 4; ++jx, g += rs) {
+                        V r = V(0);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k)
+                            r = (k == 0) ? wq[0] * g[0] : fma(wq[k], g[k], r);
+                        acc = (jx == 0) ? wx[0] * r : fma(wx[jx], r, acc);
+                    }
+                    out[(int64_t)rel * n_u + u] = ok ? acc : fwd::quiet_nan<V>();
+                }
+            }
+        }
+    }
+}
+
+// The cut of every member of a set, one workgroup each: a team evaluates many
+// members in turn, and would make each one's cut anew (9 us a member).
+template <int VS>
+__global__ __launch_bounds__(kRouteBlock<double>) void route_cut_kernel(const RouteArgs a)
+{
+    extern __shared__ uint4 smem4[];
+    char *sm = reinterpret_cast<char *>(smem4);
+    const MemberDev md = member(a, blockIdx.x);
+    const RoutePlan plan = route_plan(md.nx, md.nq, md.ax.nbuckets, md.aq.nbuckets, a.n_u, VS, 0);
+    const int ns = plan.split ? md.nq : md.nx;
+    if (plan.pieces < 2)
+        return;
+    RouteCut *rc = reinterpret_cast<RouteCut *>(sm);
+    double *kn = reinterpret_cast<double *>(sm + route_round16(sizeof(RouteCut)));
+    make_cut<kRouteBlock<double>>(rc, kn, reinterpret_cast<int *>(kn + ns),
+             (gptr<double>)(plan.split ? md.aq.knots : md.ax.knots), ns, plan.most,
+             plan.split ? a.q : a.x, plan.split && a.q_is_q, a.n, a.team_size);
+    if (threadIdx.x < sizeof(RouteCut) / 4)
+        reinterpret_cast<int *>(a.cuts + blockIdx.x)[threadIdx.x] =
+            reinterpret_cast<const int *>(rc)[threadIdx.x];
+}
+
+template <typename V, bool AS>
+hipError_t go(const RouteArgs &a, hipStream_t s)
+{
+    auto fn = xfx_route_kernel<V, AS>;
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)kLdsLimit);
+    if (e != hipSuccess)
+        return e;
+    if (a.cuts) {
+        // ns doubles and ns ints of the longest axis, as loaded (4096 knots at most)
+        const size_t lds = route_round16(sizeof(RouteCut)) + (size_t)a.longest * 12;
+        hipLaunchKernelGGL((route_cut_kernel<(int)sizeof(V)>), dim3((unsigned)a.n_mem),
+                           dim3(kRouteBlock<double>), lds, s, a);
+        if ((e = hipGetLastError()) != hipSuccess)
+            return e;
+    }
+    hipLaunchKernelGGL(fn, dim3((unsigned)(a.teams * a.team_size)), dim3(kRouteBlock<V>), kLdsLimit,
+                       s, a);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_route(const RouteArgs &a, bool f32, hipStream_t s)
+{
+    if (a.as_out)
+        return f32 ? go<float, true>(a, s) : go<double, true>(a, s);
+    return f32 ? go<float, false>(a, s) : go<double, false>(a, s);
+}
+
+}  // namespace pdfx
