@@ -330,6 +330,8 @@ int pdfx_set_dy_launch(pdfx_grid *g, int prec, int32_t block, int32_t ppt);
  * at the clamped point in CLAMP mode (f = xf / x at the clamped x).  The pairs
  * may touch at most 6 flavour groups in FP64 (2 partons each in grid order)
  * and 3 in FP32 (4 each): every pair of an 11-parton grid qualifies.
+ * One Q2 for every point (q2 NULL) is evaluated along x alone, the Q2 sums being
+ * formed once per x knot, unless pdfx_set_lumi_launch has set a shape.
  * Asynchronous on stream. */
 int pdfx_eval_lumi(const pdfx_grid *g, const void *xf_dev, int prec, int32_t n_pair,
                    const int32_t *pid_a, const int32_t *pid_b, const double *coef,

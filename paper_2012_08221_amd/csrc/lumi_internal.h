@@ -33,6 +33,29 @@ struct LumiArgs {
     unsigned long long *dom_count;
 };
 
+// The same at one Q^2: pairs by rows of the lines (each distinct parton once).
+struct LumiLineArgs {
+    AxisDev ax, aq;
+    int nx, nq;
+    const void *vals;             // value (f, i, k) at f * flav_stride + i * x_stride + k
+    size_t flav_stride;
+    int x_stride;
+    int n_row;
+    int row[kMaxReq];             // grid row of line r
+    int n_pair;
+    int ia[kLumiMaxPairs];        // line of a_k, or -1 (a parton of the pair absent: L_k = 0)
+    int ib[kLumiMaxPairs];        // line of b_k
+    double coef[kLumiMaxPairs];   // c_k
+    const double *x1, *x2;
+    double q2_fixed;
+    int64_t n;
+    void *out_pair, *out_sum;
+    int domain_mode;
+    unsigned long long *dom_count;
+};
+hipError_t launch_lumi_line(const LumiLineArgs &a, bool f32, int cus, hipStream_t s);
+bool lumi_line_fits(int nx, int nbx, int n_row, bool f32);
+
 bool lumi_supported(int nx, int nq, int nbx, int nbq);
 bool lumi_shape_supported(LaunchShape ls, bool f32);
 hipError_t launch_lumi(const LumiArgs &a, bool f32, LaunchShape ls, int cus, hipStream_t s);

@@ -1,0 +1,174 @@
+// Flavour-pair luminosity at one Q^2 for every point (the single-top example of
+// Fig. 4): with Q^2 fixed, the sum over the four Q^2 knots of a stencil is the same
+// for every point of an x interval, so a workgroup forms it once per x knot and
+// parton and a parton at a point is 4 values instead of 16.
+//
+// Same weights and the same order of sums as the kernel that walks the flavour
+// groups (the Q^2 sum inside, the x sum outside), so the same bits.  Bound by the
+// vector ALU: two FP64 logarithms, bins, weights and a division a point.  4 pairs,
+// 4 million points, sum only: 304 -> 70 us FP64, 239 -> 59 us FP32; 25 pairs 544 ->
+// 236 and 361 -> 142 us.
+#include "lumi_internal.h"
+#include "piece_axis.h"
+
+namespace pdfx {
+
+namespace {
+
+using namespace piece;
+
+constexpr int kLineBlock = 256;
+
+// Placement in LDS: the partons' lines [n_row][nx], then the x tables.
+size_t line_lds(int nx, int nbx, int n_row, bool f32)
+{
+    return (size_t)route_round16(n_row * nx * (f32 ? 4 : 8)) + route_axis_bytes(nx - 1, nbx);
+}
+
+template <typename V>
+__global__ __launch_bounds__(kLineBlock) void lumi_line_kernel(const LumiLineArgs a)
+{
+    constexpr bool F32 = sizeof(V) == 4;
+    constexpr int C = 16 / (int)sizeof(V);   // pairs stored at once
+    extern __shared__ uint4 smem4[];
+    char *sm = reinterpret_cast<char *>(smem4);
+    V *const line = reinterpret_cast<V *>(sm);
+    const int tid = threadIdx.x;
+    const int nx = a.nx, nq = a.nq;
+
+    int off = route_round16(a.n_row * nx * (int)sizeof(V));
+    const PieceAxis px = place_axis(sm, off, a.ax, 0, nx - 1);
+    {
+        const PieceAxis both[2] = {px, px};
+        const AxisDev *const axes[2] = {&a.ax, &a.ax};
+        load_axes<F32, kLineBlock>(both, axes);
+    }
+
+    // Q^2: inside, clamped into the grid, or (every point outside) the first knot
+    double q2 = a.q2_fixed;
+    const bool q_in = q2 >= a.aq.lo && q2 <= a.aq.hi;
+    if (!q_in)
+        q2 = a.domain_mode == 1 ? fmin(fmax(q2, a.aq.lo), a.aq.hi) : a.aq.lo;
+    V wq[4];
+    const double lnq = log(q2);
+    const int cq = window4(far_weights<V>(a.aq, q2, lnq, wq), nq, wq);
+    const V *const src = reinterpret_cast<const V *>(a.vals);
+    for (int e = tid; e < a.n_row * nx; e += kLineBlock) {
+        const int r = e / nx, i = e - r * nx;
+        const V *v = src + (size_t)a.row[r] * a.flav_stride + (size_t)i * a.x_stride + cq;
+        V t = wq[0] * v[0];
+        t = fma(wq[1], v[1], t);
+        t = fma(wq[2], v[2], t);
+        t = fma(wq[3], v[3], t);
+        line[e] = t;
+    }
+    __syncthreads();
+
+    V *const out_pair = reinterpret_cast<V *>(a.out_pair);
+    V *const out_sum = reinterpret_cast<V *>(a.out_sum);
+    const int n_pair = a.n_pair;
+    const int64_t step = (int64_t)gridDim.x * kLineBlock;
+    int64_t p = (int64_t)blockIdx.x * kLineBlock + tid;
+    const int64_t n_wave = (a.n + 63) / 64 * 64;   // whole waves, for the counting
+    double nx1 = load_point(a.x1, p, a.n), nx2 = load_point(a.x2, p, a.n);
+    for (; p < n_wave; p += step) {
+        double x1 = nx1, x2 = nx2;
+        nx1 = load_point(a.x1, p + step, a.n);
+        nx2 = load_point(a.x2, p + step, a.n);
+        const bool nan_in = (x1 != x1) || (x2 != x2);
+        bool ok = x1 >= px.lo && x1 <= px.hi && x2 >= px.lo && x2 <= px.hi && q_in;
+        if (!ok) {
+            if (a.domain_mode == 1 && !nan_in) {
+                ok = true;
+                x1 = fmin(fmax(x1, px.lo), px.hi);
+                x2 = fmin(fmax(x2, px.lo), px.hi);
+            } else {
+                x1 = x2 = px.lo;
+            }
+        }
+        const bool live = p < a.n;
+        fwd::count_flagged(live && !ok, a.dom_count);
+        const double ln1 = log(x1), ln2 = log(x2);
+        V w1[4], w2[4];
+        int i1 = piece_bin(px, x1, ln1), i2 = piece_bin(px, x2, ln2);
+        piece_weights<V>(px, i1, ln1, w1);
+        piece_weights<V>(px, i2, ln2, w2);
+        i1 = window4(i1, nx, w1);
+        i2 = window4(i2, nx, w2);
+        V inv = (V)(1.0 / (x1 * x2));
+        inv = ok ? inv : fwd::quiet_nan<V>();
+        auto at = [&](int row, int i, const V w[4]) {
+            const V *v = line + row * nx + i;
+            V t = w[0] * v[0];
+            t = fma(w[1], v[1], t);
+            t = fma(w[2], v[2], t);
+            return fma(w[3], v[3], t);
+        };
+        V sum = V(0), fa = V(0);
+        int row_a = -1;
+        for (int k0 = 0; k0 < n_pair; k0 += C) {
+            V l[C];
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                l[c] = V(0);
+                if (k0 + c < n_pair) {
+                    const int ia = a.ia[k0 + c], ib = a.ib[k0 + c];
+                    if (ia >= 0) {
+                        if (ia != row_a)
+                            fa = at(ia, i1, w1);
+                        row_a = ia;
+                        l[c] = fa * at(ib, i2, w2) * inv;
+                    }
+                    sum = fma((V)a.coef[k0 + c], l[c], sum);
+                }
+            }
+            if (out_pair && live) {
+                V *dst = out_pair + p * n_pair + k0;
+                if (k0 + C <= n_pair) {
+                    typedef V vec __attribute__((ext_vector_type(C), aligned(sizeof(V))));
+                    vec v;
+#pragma unroll
+                    for (int c = 0; c < C; ++c)
+                        v[c] = l[c];
+                    *reinterpret_cast<vec *>(dst) = v;
+                } else {
+#pragma unroll
+                    for (int c = 0; c < C - 1; ++c)
+                        if (k0 + c < n_pair)
+                            dst[c] = l[c];
+                }
+            }
+        }
+        if (out_sum && live)
+            out_sum[p] = ok ? sum : fwd::quiet_nan<V>();
+    }
+}
+
+}  // namespace
+
+hipError_t launch_lumi_line(const LumiLineArgs &a, bool f32, int cus, hipStream_t s)
+{
+    const size_t lds = line_lds(a.nx, a.ax.nbuckets, a.n_row, f32);
+    int64_t grid = (a.n + kLineBlock - 1) / kLineBlock;
+    const int64_t most = (int64_t)cus * 8;   // 32 waves a compute unit
+    if (grid > most)
+        grid = most;
+    if (grid < 1)
+        return hipSuccess;
+    auto go = [&](auto fn) -> hipError_t {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess)
+            return e;
+        hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(kLineBlock), lds, s, a);
+        return hipGetLastError();
+    };
+    return f32 ? go(lumi_line_kernel<float>) : go(lumi_line_kernel<double>);
+}
+
+bool lumi_line_fits(int nx, int nbx, int n_row, bool f32)
+{
+    return line_lds(nx, nbx, n_row, f32) <= kLdsLimit;
+}
+
+}  // namespace pdfx

@@ -205,3 +205,35 @@ def test_fixed_q2_matches_per_point_array(pdf, grid, torch, prec, domain):
     finally:
         pdf.set_lumi_launch(prec, *keep)
 
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32s"])
+@pytest.mark.parametrize("n_pair", [1, 2, 3, 4, 5, 121])
+def test_one_scale_by_lines_equals_the_group_kernel(grid, torch, n_pair, prec):
+    """One Q^2 without a set shape (lines along x) against a set shape (flavour groups)."""
+    from paper_2012_08221_amd import api
+    g = grid
+    rng = np.random.default_rng(n_pair)
+    a = rng.choice(np.r_[g.pids, 22], n_pair)
+    b = rng.choice(g.pids, n_pair)
+    if n_pair == 121:
+        a, b = np.repeat(g.pids, 11), np.tile(g.pids, 11)
+    coef = rng.standard_normal(n_pair)
+    pdf, grp = api.PDF(g), api.PDF(g)
+    grp.set_lumi_launch(prec, 512, 1)
+    vals = torch.as_tensor(g.xf * 1.5, dtype=api.prec_dtype(prec), device="cuda")
+    for n in (1, 63, 64, 65, 5000):
+        x1, x2 = (torch.as_tensor(np.exp(rng.uniform(np.log(1e-9), 0.0, n)), device="cuda")
+                  for _ in range(2))
+        if n > 64:
+            x1[:100:7] = torch.as_tensor(g.x[-1], device="cuda")
+            x2[3:100:11] = float(g.x[0])
+            x1[5:100:13] = 1.5
+            x2[::17] = float("nan")
+        for q2 in (172.5 ** 2, float(g.q2[0]), float(g.q2[-1]), 4.92 ** 2, 0.5):
+            for domain in ("nan", "clamp"):
+                for v in (None, vals):
+                    kw = dict(q2_fixed=q2, coef=coef, prec=prec, domain=domain, values=v)
+                    for u, w in zip(pdf.lumi(a, b, x1, x2, **kw), grp.lumi(a, b, x1, x2, **kw)):
+                        np.testing.assert_array_equal(u.cpu().numpy(), w.cpu().numpy())
+                    assert pdf.domain_errors() == grp.domain_errors()
