@@ -257,7 +257,11 @@ int pdfx_eval_set_xfx(const pdfx_set *s, int prec, const int32_t *pids, int32_t 
  *           call writes the number of partial sums it produces to *n_blocks
  *           if n_blocks is non-NULL (query with n = 0 first to size it:
  *           it is at most pdfx_dy_max_blocks()).
- * Requires the grid's alpha_s knots and owned values (or xf_dev). */
+ * Requires the grid's alpha_s knots and owned values (or xf_dev).
+ * Large calls (from 400 thousand points; 2 million where the Q^2 axis needs many
+ * pieces) on a grid whose alpha_s knots are its Q^2 knots go to the routed kernel,
+ * unless pdfx_set_dy_launch has set a shape: the same I, bit for bit, and other
+ * partial sums of it. */
 int pdfx_eval_dy(const pdfx_grid *g, const void *xf_dev, int prec,
                  const double *u1, const double *u2, int64_t n,
                  double xmin, double s, void *out, double *block_sums,

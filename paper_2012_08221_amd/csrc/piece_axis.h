@@ -1,5 +1,6 @@
-// Search tables of a part of an axis in LDS: bins, folded weights and windows of
-// the kernels that keep their part of the grid resident.
+// Parts of the kernels that keep a piece of the grid in LDS: the search tables of a
+// part of an axis, bins, folded weights, windows and stencils, and the cut of an
+// axis into pieces.
 #pragma once
 
 #include "route_internal.h"
@@ -186,6 +187,202 @@ __device__ __forceinline__ int far_weights(const AxisDev &ax, double v, double l
         fwd::fold<float>(t, f[2], f[3], f[4], f[5], f[6], f[7], w);
     }
     return i;
+}
+
+// The lane, recomputed where it is used: what is derived from it is then not
+// kept in registers across the loops, which have none to spare.
+__device__ __forceinline__ int fresh_lane()
+{
+    int l;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+    return l;
+}
+
+// K values of V side by side in LDS.
+template <typename V, int K>
+__device__ __forceinline__ void lds_values(const char *p, V v[K])
+{
+    if constexpr (sizeof(V) * K == 16) {
+        const uint4 d = *reinterpret_cast<const uint4 *>(p);
+        __builtin_memcpy(v, &d, 16);
+    } else if constexpr (sizeof(V) * K == 8) {
+        const uint2 d = *reinterpret_cast<const uint2 *>(p);
+        __builtin_memcpy(v, &d, 8);
+    } else {
+        v[0] = *reinterpret_cast<const V *>(p);
+    }
+}
+
+// 16-tap stencil of the K rows of one plane at node address p (bytes), rows
+// row_bytes apart.
+template <typename V, int K>
+__device__ __forceinline__ void plane_stencil(const char *p, int row_bytes, const V wx[4],
+                                              const V wq[4], V acc[K])
+{
+    constexpr int NB = (int)sizeof(V) * K;
+#pragma unroll
+    for (int jx = 0; jx < 4; ++jx) {
+        V r[K];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            V v[K];
+            lds_values<V, K>(p + jx * row_bytes + k * NB, v);
+#pragma unroll
+            for (int g = 0; g < K; ++g)
+                r[g] = (k == 0) ? wq[0] * v[g] : fma(wq[k], v[g], r[g]);
+        }
+#pragma unroll
+        for (int g = 0; g < K; ++g)
+            acc[g] = (jx == 0) ? wx[0] * r[g] : fma(wx[jx], r[g], acc[g]);
+        // eight reads in flight a wave: with 16 waves that fills the LDS pipe, and
+        // sixteen would not fit the 128 registers
+        if (jx == 1)
+            asm volatile("" ::: "memory");
+    }
+}
+
+// Shares team_size workgroups among the pieces by weight w (one lane per
+// piece, pieces <= team_size): at least one each, the others to the piece with
+// the largest weight per workgroup.  Returns the lane's number.
+__device__ __forceinline__ int share_out(float w, int pieces, int team_size)
+{
+    const int lane = threadIdx.x & 63;
+    float sum = lane < pieces ? w : 0.f;
+    for (int d = 32; d; d >>= 1)
+        sum += __shfl_xor(sum, d);
+    int mine = lane < pieces ? (int)(w / sum * (float)team_size) : 0;
+    if (lane < pieces && mine < 1)
+        mine = 1;
+    int total = mine;
+    for (int d = 32; d; d >>= 1)
+        total += __shfl_xor(total, d);
+    // too many (pieces raised to one): from the lightest load; too few: to the heaviest
+    while (total != team_size) {
+        const bool more = total < team_size;
+        float key = -1.f;
+        if (lane < pieces)
+            key = more ? w / (float)mine : (mine > 1 ? 1.f / (w / (float)(mine - 1) + 1e-30f) : -1.f);
+        int at = lane;
+        for (int d = 32; d; d >>= 1) {
+            const float k2 = __shfl_xor(key, d);
+            const int a2 = __shfl_xor(at, d);
+            if (k2 > key || (k2 == key && a2 < at)) {
+                key = k2;
+                at = a2;
+            }
+        }
+        if (lane == at)
+            mine += more ? 1 : -1;
+        total += more ? 1 : -1;
+    }
+    return mine;
+}
+
+constexpr int kRouteSamples = 1024;
+
+// Makes the cut of an axis of ns knots for pieces of at most `most` intervals.
+// knot(i): the i-th knot; sample(k): the k-th sampled point's coordinate, on the
+// same scale.  kn, cum: LDS for ns doubles and ns ints.  Every workgroup of the
+// team makes the same cut from the same samples.
+template <int BLOCK, typename Knot, typename Sample>
+__device__ __forceinline__ void make_cut(RouteCut *rc, double *kn, int *cum, int ns, int most,
+                                         int team_size, Knot knot, Sample sample)
+{
+    constexpr int S = kRouteSamples, PER = (S + BLOCK - 1) / BLOCK;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));   // nothing of this is kept in registers beyond it
+    const int lane = tid & 63;
+    const int ni = ns - 1;
+    double v[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k)
+        v[k] = sample(min(k * BLOCK + tid, S - 1));
+    for (int i = tid; i < ns; i += BLOCK) {
+        kn[i] = knot(i);
+        cum[i] = 0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        if (k * BLOCK + tid >= S)
+            break;
+        const double u = v[k];
+        int lo = 0, hi = ni;              // interval in [lo, hi)
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (u >= kn[mid])
+                lo = mid;
+            else
+                hi = mid;
+        }
+        atomicAdd(&cum[lo], 1);
+    }
+    __syncthreads();
+    if (tid < 64) {
+        // running sums: cum[i] = samples in intervals [0, i]
+        const int per = (ni + 63) / 64;
+        int own = 0;
+        for (int i = lane * per; i < (lane + 1) * per && i < ni; ++i) {
+            own += cum[i];
+            cum[i] = own;
+        }
+        int incl = own;
+        for (int d = 1; d < 64; d <<= 1) {
+            const int o = __shfl_up(incl, d);
+            incl += lane >= d ? o : 0;
+        }
+        for (int i = lane * per; i < (lane + 1) * per && i < ni; ++i)
+            cum[i] += incl - own;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        // first interval with more than c samples up to and in it, or ni
+        auto reach = [&](int c) {
+            int lo = 0, hi = ni;
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (cum[mid] > c)
+                    hi = mid;
+                else
+                    lo = mid + 1;
+            }
+            return lo;
+        };
+        int a = reach(0), b = reach(S - 1) + 1;
+        const int pieces = (b - a + most - 1) / most;
+        // room left in the pieces goes to the intervals beyond, half to either side
+        int spare = pieces * most - (b - a);
+        const int down = min(a, max(spare / 2, spare - (ni - b)));
+        a -= down;
+        spare -= down;
+        b += min(ni - b, spare);
+        const int below = a > 0 ? cum[a - 1] : 0, inside = cum[b - 1] - below;
+        // equal shares of the samples, as far as `most` allows
+        int want = reach(below + (int)((int64_t)inside * lane / pieces) - 1) + 1;
+        int cut = a;
+        for (int k = 1; k < pieces; ++k) {
+            const int prev = __shfl(cut, k - 1), w = __shfl(want, k);
+            int c = max(w, max(prev + 1, b - (pieces - k) * most));
+            c = min(c, min(prev + most, b - (pieces - k)));
+            if (lane == k)
+                cut = c;
+        }
+        if (lane >= pieces)
+            cut = b;
+        const int next = __shfl(cut, lane < 63 ? lane + 1 : 63);
+        // a scan costs about 1/32 of an evaluation per point and piece
+        const int held = lane < pieces ? cum[next - 1] - (cut > 0 ? cum[cut - 1] : 0) : 0;
+        const int width = share_out((float)held + (float)S * (1.f / 32.f), pieces, team_size);
+        if (lane < pieces) {
+            rc->cut[lane] = cut;
+            rc->width[lane] = width;
+        }
+        if (lane == 0) {
+            rc->pieces = pieces;
+            rc->cut[pieces] = b;
+        }
+    }
+    __syncthreads();
 }
 
 }  // namespace piece

@@ -13,6 +13,7 @@
 #include "pdfx_internal.h"
 #include "runtime_internal.h"
 #include "route_internal.h"
+#include "dy_route.h"
 #include "lumi_internal.h"
 #include "extrap_internal.h"
 #include "bwd_internal.h"
@@ -648,6 +649,7 @@ int pdfx_set_dy_launch(pdfx_grid *g, int prec, int32_t block, int32_t ppt)
     LaunchShape ls{block, ppt};
     if (!dy_shape_supported(ls, prec == PDFX_F32S))
         return fail(PDFX_EINVAL, "integrand launch shape (%d, %d) not compiled", block, ppt);
+    g->dy_pinned[prec] = true;
     g->dy_shape[prec] = ls;
     return PDFX_OK;
 }
@@ -1837,6 +1839,52 @@ int pdfx_eval_dy(const pdfx_grid *g, const void *xf_dev, int prec, const double 
     int nb = 0;
     hipError_t e;
     const bool f32 = prec == PDFX_F32S;
+    const int np = a.n_seq / 2;
+    const int most = g->alphas_on_q ? dy_route_most(a.nx, a.nq, a.ax.nbuckets, a.aq.nbuckets, np,
+                                                    f32)
+                                    : 0;
+    const int pieces = most > 0 ? (a.nq - 1 + most - 1) / most : 0;
+    if (!g->dy_pinned[prec] && most > 0 && n >= (pieces <= 5 ? kDyRouteMin : kDyRouteMinMany)) {
+        DyRouteArgs r{};
+        RouteArgs t{};
+        route_teams(g->cus, &t);
+        r.teams = t.teams;
+        r.team_size = t.team_size;
+        r.range_pts = ((n + r.teams - 1) / r.teams + 63) / 64 * 64;
+        if (pieces <= std::min(kRouteMaxPieces, r.team_size) && r.range_pts <= (1 << 30)) {
+            r.ax = a.ax;
+            r.aq = a.aq;
+            r.nx = a.nx;
+            r.nq = a.nq;
+            r.x_stride = xf_dev ? a.nq : a.nq + 2;
+            r.flav_stride = xf_dev ? (size_t)a.nx * a.nq : (size_t)a.slab_elems;
+            r.vals = xf_dev ? xf_dev
+                            : (const char *)g->vals[prec].ptr +
+                                  (size_t)(r.x_stride + 1) * (f32 ? 4 : 8);
+            r.as_vals = a.as_vals;
+            r.np = np;
+            for (int u = 0; u < np; ++u) {
+                r.row[u] = a.seq_row[2 * u];
+                r.row[np + u] = a.seq_row[2 * u + 1];
+            }
+            r.most = most;
+            r.u1 = u1;
+            r.u2 = u2;
+            r.n = n;
+            r.lnxmin = a.lnxmin;
+            r.lnrange = a.lnrange;
+            r.s = s;
+            r.L2 = a.L2;
+            r.out = out;
+            r.block_sums = block_sums;
+            r.dom_count = a.dom_count;
+            if ((e = launch_dy_route(r, f32, (hipStream_t)stream)) != hipSuccess)
+                return fail_hip(e, "integrand launch");
+            if (n_blocks)
+                *n_blocks = r.teams * r.team_size;
+            return PDFX_OK;
+        }
+    }
     if (dy_dma_ok(g)) {
         // double-buffered kernel over the flavour groups of the grid
         a.gvals = g->dvals[prec].ptr;

@@ -83,6 +83,7 @@ struct pdfx_grid {
     // to give every other compute unit a tile)
     bool shape_pinned[2] = {false, false};
     pdfx::LaunchShape dy_shape[2] = {{512, 1}, {512, 2}};   // double-buffered integrand kernel
+    bool dy_pinned[2] = {false, false};      // dy_shape set by pdfx_set_dy_launch
     pdfx::LaunchShape lumi_shape[2] = {{512, 2}, {512, 2}};  // flavour-pair luminosity kernel
     bool lumi_pinned[2] = {false, false};    // lumi_shape set by pdfx_set_lumi_launch
     mutable pdfx::DeviceBuf bwd_ws;          // adjoint workspace (grows on demand)

@@ -170,3 +170,65 @@ def test_against_the_oracle(api, torch, prec, tol):
     ref = oracle.xfx(g, g.pids, xs, qs)
     M = oracle.stencil_absmax(g, g.pids, xs, qs)
     assert capped_rel_err(got[at], ref, M).max() <= tol
+
+
+# ---- the routed integrand ----
+
+def dy_both(api, torch, g, u1, u2, prec, **kw):
+    routed, cycled = api.PDF(g), api.PDF(g)
+    cycled.set_dy_launch(prec, 512, 1)
+    (a, sa), (b, sb) = (api.dy_integrand(p, u1, u2, prec=prec, **kw) for p in (routed, cycled))
+    equal(a, b)
+    assert routed.domain_errors() == cycled.domain_errors()
+    if not torch.isnan(a).any():
+        # both sum the same values in FP64, in another order
+        bound = a.shape[0] * 2.0 ** -53 * float(a.double().abs().sum())
+        assert abs(float(sa.sum()) - float(sb.sum())) <= bound
+    return a
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32s"])
+@pytest.mark.parametrize("geo", [(100, 3, 50), (60, 2, 30), (62, 4, 79), (100, 4, 48), (40, 2, 120), (9, 2, 8)])
+def test_integrand_same_bits(api, torch, geo, prec):
+    nx, nsub, nq = geo
+    g = wl.make_grid(wl.draw_params(np.random.default_rng(11)), nx, wl.MEMBER_EDGES[nsub], nq)
+    gen = torch.Generator(device="cuda").manual_seed(12)
+    u1, u2 = (torch.rand(N, generator=gen, device="cuda", dtype=torch.float64) for _ in range(2))
+    # products of x on and beside the thresholds and the ends of the Q^2 axis
+    k = 0
+    for q2 in list(g.q2[np.array(g.q_off[1:-1])]) + [g.q2[0], g.q2[-1]]:
+        lim = np.log(q2 / 13000.0 ** 2) / np.log(1e5) + 2.0      # u1 + u2 at this Q^2
+        v = torch.linspace(max(0.0, lim - 1.0), min(1.0, lim), 2000, device="cuda", dtype=torch.float64)
+        for d in (-1e-15, 0.0, 1e-15):
+            u1[k:k + 2000], u2[k:k + 2000] = v, (lim - v + d).clamp(0.0, 1.0)
+            k += 2000
+    dy_both(api, torch, g, u1, u2, prec)
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32s"])
+def test_integrand_odd_inputs(api, torch, prec):
+    g = wl.make_grid(wl.draw_params(np.random.default_rng(13)), 100, wl.MEMBER_EDGES[3], 50)
+    gen = torch.Generator(device="cuda").manual_seed(14)
+    u1, u2 = (torch.rand(N, generator=gen, device="cuda", dtype=torch.float64) for _ in range(2))
+    u1[::1001] = 1.5        # x > 1: outside
+    u2[7::1003] = float("nan")
+    dy_both(api, torch, g, u1, u2, prec)
+    vals = torch.as_tensor(g.xf * 0.75, dtype=api.prec_dtype(prec), device="cuda")
+    dy_both(api, torch, g, u1, u2, prec, values=vals)
+    # all sampled points at high Q^2, a few of the others anywhere
+    far = torch.rand(N, device="cuda") < 0.01
+    for s in (1024, 768, 1536):
+        far[(torch.arange(s, device="cuda") * N) // s] = False
+    v1, v2 = (torch.where(far, u, 0.9 + 0.1 * u.nan_to_num(0.5).clamp(0.0, 1.0)) for u in (u1, u2))
+    dy_both(api, torch, g, v1, v2, prec)
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32s"])
+@pytest.mark.parametrize("quarks", [1, 2, 3, 4])
+def test_integrand_fewer_quarks(api, torch, quarks, prec):
+    g = wl.make_grid(wl.draw_params(np.random.default_rng(15)), 60, wl.MEMBER_EDGES[3], 40)
+    keep = [i for i, p in enumerate(g.pids) if p == 21 or abs(p) <= quarks]
+    g.pids, g.xf = g.pids[keep], np.ascontiguousarray(g.xf[keep])
+    gen = torch.Generator(device="cuda").manual_seed(16)
+    u1, u2 = (torch.rand(N, generator=gen, device="cuda", dtype=torch.float64) for _ in range(2))
+    dy_both(api, torch, g, u1, u2, prec)
