@@ -161,7 +161,7 @@ __global__ __launch_bounds__(kDyRouteBlock) void dy_route_kernel(const DyRouteAr
     {
         const PieceAxis both[2] = {px, pq};
         const AxisDev *const axes[2] = {&a.ax, &a.aq};
-        load_axes<F32, kDyRouteBlock>(both, axes);
+        load_axes<F32>(both, axes, kDyRouteBlock);
     }
     const V *asv = reinterpret_cast<const V *>(sm + off) + 1;   // padded by one on each side
     for (int i = tid; i < nq + 2; i += kDyRouteBlock)

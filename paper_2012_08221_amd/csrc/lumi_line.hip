@@ -41,7 +41,7 @@ __global__ __launch_bounds__(kLineBlock) void lumi_line_kernel(const LumiLineArg
     {
         const PieceAxis both[2] = {px, px};
         const AxisDev *const axes[2] = {&a.ax, &a.ax};
-        load_axes<F32, kLineBlock>(both, axes);
+        load_axes<F32>(both, axes, kLineBlock);
     }
 
     // Q^2: inside, clamped into the grid, or (every point outside) the first knot

@@ -275,6 +275,10 @@ hipError_t xfx_dma_occupancy_f32s(LaunchShape ls, int *blocks_per_cu);
 bool dma_supported(LaunchShape ls, int nx, int nq, int nbx, int nbq, bool f32 = false);
 // The alpha_s values of a Q^2 axis of nq knots fit the kernel's LDS after the knots.
 bool dma_alphas_fit(int nx, int nq, bool f32);
+// Direct kernel for small calls (raw: a.vals are caller values; otherwise a.gvals
+// the bordered group slabs); stages and slots planned as for the group kernels.
+bool xfx_direct_fits(const XfxArgs &a);
+hipError_t launch_xfx_direct(const XfxArgs &a, bool f32, bool raw, hipStream_t s);
 hipError_t launch_alphas(const AlphasArgs &a, bool f32, hipStream_t s);
 hipError_t launch_repack(const RepackArgs &a, bool f32, hipStream_t s);
 hipError_t launch_set(const SetArgs &a, bool f32, LaunchShape ls, size_t lds, int cus, hipStream_t s);

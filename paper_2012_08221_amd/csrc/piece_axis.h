@@ -113,11 +113,12 @@ __device__ __forceinline__ PieceAxis place_axis(char *sm, int &off, const AxisDe
 
 // Copies the tables of both axis parts into LDS; all loads of a thread are
 // issued before its first write.
-template <bool F32, int BLOCK>
-__device__ __forceinline__ void load_axes(const PieceAxis (&p)[2], const AxisDev *const (&ax)[2])
+template <bool F32>
+__device__ __forceinline__ void load_axes(const PieceAxis (&p)[2], const AxisDev *const (&ax)[2],
+                                          int block)
 {
     const int most = max(max(p[0].cnt + 1, p[0].nb / 2), max(p[1].cnt + 1, p[1].nb / 2));
-    for (int i = threadIdx.x; i < most; i += BLOCK) {
+    for (int i = threadIdx.x; i < most; i += block) {
         double k[2], z[2][2], c64[2][2];
         float c32[2][4];
         unsigned int sd[2];
@@ -239,6 +240,31 @@ __device__ __forceinline__ void plane_stencil(const char *p, int row_bytes, cons
         if (jx == 1)
             asm volatile("" ::: "memory");
     }
+}
+
+// The lane's register of another lane of its quad.
+template <int CTRL>
+__device__ __forceinline__ uint32_t quad_lane(uint32_t v)
+{
+    return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, 0xf, true);
+}
+
+// Exchanges between lanes l and l ^ D (D = 1, 2) the 16-byte pieces c0 of the
+// lanes with that bit set against the c1 of the others.
+template <int D>
+__device__ __forceinline__ void swap_pieces(int lane, uint4 &c0, uint4 &c1)
+{
+    constexpr int CTRL = D == 1 ? 0xB1 : 0x4E;   // quad_perm [1,0,3,2], [2,3,0,1]
+    const bool up = lane & D;
+    auto one = [&](uint32_t &a, uint32_t &b) {
+        const uint32_t fa = quad_lane<CTRL>(a), fb = quad_lane<CTRL>(b);
+        a = up ? fb : a;
+        b = up ? b : fa;
+    };
+    one(c0.x, c1.x);
+    one(c0.y, c1.y);
+    one(c0.z, c1.z);
+    one(c0.w, c1.w);
 }
 
 // Shares team_size workgroups among the pieces by weight w (one lane per

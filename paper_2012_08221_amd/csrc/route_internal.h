@@ -107,6 +107,14 @@ struct RouteArgs {
 // 37 / 32 us routed, 512 thousand 57 / 38 and 52 / 40.  Larger grids (190 x 75):
 // 128 thousand 45 / 24 and 38 / 30, 256 thousand 81 / 43 and 47 / 36.
 constexpr int64_t kRouteMinDma = 400000, kRouteMinOther = 200000;
+// Points times flavour groups up to which a call on a grid of the double-buffered
+// kernel goes to the direct kernel; calls on larger grids do so until they are
+// routed.  100 x 50 knots, 11 partons in 6 groups (FP64) / 3 (FP32), double-buffered
+// and direct: 32 thousand points 17.8 / 13.0 us and 9.6 / 7.4, 64 thousand 18.5 /
+// 13.3 and 20.6 / 10.2, 100 thousand 19.1 / 13.8 and 27.3 / 15.3; 2 partons in 2
+// groups: 100 thousand 12.2 / 10.2 and 10.5 / 8.0.  190 x 75: 100 thousand points
+// 47.6 / 29.1 us by the single-buffer kernel and 29.4 / 16.6.
+constexpr int64_t kDirectMaxDma = 250000;
 // The same for a set: points per member and points over all members.  101
 // members in FP64 / FP32 by the class kernels and routed: 32 thousand points
 // 359 / 238 us and 415 / 280, 64 thousand 724 / 450 and 558 / 368; 8 members:

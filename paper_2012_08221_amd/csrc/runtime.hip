@@ -1064,6 +1064,20 @@ int run_xfx(const pdfx_grid *g, XfxArgs &a, const void *xf_dev, int prec, hipStr
             ls = LaunchShape{512, 1};
     }
     const bool staged = ls.ppt > 0 && plan_stages(a, f32 ? 4 : 2);
+    const int64_t direct_most = g->dma_grid ? kDirectMaxDma / std::max(a.n_stage, 1) : kRouteMinOther;
+    if (staged && !g->shape_pinned[prec] && a.n <= direct_most && xfx_direct_fits(a)) {
+        if (xf_dev) {
+            a.vals = xf_dev;
+        } else {
+            a.gvals = g->gvals[prec].ptr;
+            a.gstride = g->gstride;
+        }
+        if ((e = launch_xfx_direct(a, f32, xf_dev != nullptr, s)) != hipSuccess)
+            return fail_hip(e, "xfx launch");
+        if (as_done)
+            *as_done = a.as_out != nullptr;
+        return PDFX_OK;
+    }
     if (staged && g->dma_grid && (uintptr_t)a.out % 16 == 0 &&
         dma_supported(ls, a.nx, a.nq, a.ax.nbuckets, a.aq.nbuckets, f32)) {
         a.gvals = g->dvals[prec].ptr;

@@ -47,31 +47,6 @@ template <typename V>
 constexpr int kRouteBlock = sizeof(V) == 8 ? 768 : 1024;
 constexpr int kRouteScan = 4;      // tiles of 64 points whose coordinates are loaded at once
 
-// The lane's register of another lane of its quad.
-template <int CTRL>
-__device__ __forceinline__ uint32_t quad_lane(uint32_t v)
-{
-    return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, 0xf, true);
-}
-
-// Exchanges between lanes l and l ^ D (D = 1, 2) the 16-byte pieces c0 of the
-// lanes with that bit set against the c1 of the others.
-template <int D>
-__device__ __forceinline__ void swap_pieces(int lane, uint4 &c0, uint4 &c1)
-{
-    constexpr int CTRL = D == 1 ? 0xB1 : 0x4E;   // quad_perm [1,0,3,2], [2,3,0,1]
-    const bool up = lane & D;
-    auto one = [&](uint32_t &a, uint32_t &b) {
-        const uint32_t fa = quad_lane<CTRL>(a), fb = quad_lane<CTRL>(b);
-        a = up ? fb : a;
-        b = up ? b : fa;
-    };
-    one(c0.x, c1.x);
-    one(c0.y, c1.y);
-    one(c0.z, c1.z);
-    one(c0.w, c1.w);
-}
-
 template <int K, typename V>
 __device__ __forceinline__ void store_values(V *dst, const V v[K])
 {
@@ -235,7 +210,7 @@ __global__ __launch_bounds__(kRouteBlock<V>) void xfx_route_kernel(const RouteAr
         {
             const PieceAxis both[2] = {px, pq};
             const AxisDev *const axes[2] = {&md.ax, &md.aq};
-            load_axes<F32, BLOCK>(both, axes);
+            load_axes<F32>(both, axes, BLOCK);
         }
         const V *asv = reinterpret_cast<const V *>(sm + off) + 1;   // padded by one on each side
         if constexpr (AS) {

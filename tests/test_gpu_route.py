@@ -232,3 +232,37 @@ def test_integrand_fewer_quarks(api, torch, quarks, prec):
     gen = torch.Generator(device="cuda").manual_seed(16)
     u1, u2 = (torch.rand(N, generator=gen, device="cuda", dtype=torch.float64) for _ in range(2))
     dy_both(api, torch, g, u1, u2, prec)
+
+
+# ---- the direct kernel of small calls ----
+
+@pytest.mark.parametrize("prec", ["f64", "f32s"])
+@pytest.mark.parametrize("geo", [(100, 3, 50), (190, 4, 75), (9, 2, 8)])
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 3001])
+def test_small_calls_same_bits(api, torch, geo, n, prec):
+    nx, nsub, nq = geo
+    g = wl.make_grid(wl.draw_params(np.random.default_rng(21)), nx, wl.MEMBER_EDGES[nsub], nq)
+    direct, cycled = api.PDF(g), api.PDF(g)
+    cycled.set_launch(prec, 512, 1)
+    x, q2 = points(torch, g, n, 22)
+    if n > 64:
+        x[::7] *= 1e-2
+        q2[::11] *= 1e6
+        x[3::13] = float("nan")
+    vals = torch.as_tensor(g.xf * 1.25 + 0.5, dtype=api.prec_dtype(prec), device="cuda")
+    buf = torch.zeros(n * 11 + 1, dtype=api.prec_dtype(prec), device="cuda")
+    for domain in ("nan", "clamp"):
+        for pids in (list(g.pids), [21], [3, -5], [2, 22, 2, 0, 21, -4, 2], [22], list(g.pids[::-1])):
+            for v in (None, vals):
+                equal(direct.xfxQ2(pids, x, q2, prec=prec, domain=domain, values=v),
+                      cycled.xfxQ2(pids, x, q2, prec=prec, domain=domain, values=v))
+                assert direct.domain_errors() == cycled.domain_errors()
+        a, b = (p.xfx_alphasQ2(g.pids, x, q2, prec=prec, domain=domain) for p in (direct, cycled))
+        equal(a[0], b[0])
+        # alpha_s from the point's Q^2 weights here, in a pass of its own on the larger grid
+        np.testing.assert_allclose(a[1].cpu().numpy(), b[1].cpu().numpy(),
+                                   rtol=1e-14 if prec == "f64" else 1e-6)
+        assert direct.domain_errors() == cycled.domain_errors()
+        out = buf[1:].view(n, 11)
+        direct.xfxQ(g.pids, x, q2.sqrt(), prec=prec, domain=domain, out=out)
+        equal(out, cycled.xfxQ(g.pids, x, q2.sqrt(), prec=prec, domain=domain))
