@@ -14,6 +14,7 @@
 #include "bwd_internal.h"
 #include "xfx_dma_impl.h"
 #include "fixed_point.h"
+#include "scatter_order.h"
 
 namespace pdfx {
 
@@ -284,13 +285,13 @@ __global__ __launch_bounds__(BLOCK) void coord_grad_kernel(const CoordArgs c)
 // rather than once per flavour.  The LDS sums are added to the FP64
 // accumulator at the end.
 //
-// Each wave takes 64 consecutive points per step.  A point's 16 adds go to
-// its stencil base plus offsets common to all lanes, so the wave first deals
-// its points out to lanes by the base's bank (wave_deal); the keys for that
-// are loaded a step ahead, so that only the dealt point's own values are
-// waited for.  The interval records are read from global memory (they stay
-// in the L1 cache): the LDS is the pass's bottleneck, and records staged
-// there made it slower.  The sums are kept in 64-bit fixed point
+// A point's 16 adds are made in its lane's own order over a blocked layout
+// (scatter_order.h), so that the lanes of an add hit different banks; the next
+// step's state is loaded a step ahead.  The two constants of each interval that the
+// weights need are in LDS (the records in global memory, eight gathers a point,
+// kept the pass waiting).  1e6 points x 11 FP32 flavours on 100 x 50 knots: 76 us, 41
+// of them vector instructions and 27 LDS adds (the adds in one order, lanes dealt over
+// the banks by their windows instead: 83 us).  The sums are kept in 64-bit fixed point
 // (fixed_point.h), with the scale of each flavour taken from the max of
 // finite |dL/dout| (left per workgroup by the coordinate pass, else found by
 // a sweep over the chunk) and from the axes' weight-sum bounds.  A non-finite
@@ -301,20 +302,26 @@ __global__ __launch_bounds__(BLOCK) void coord_grad_kernel(const CoordArgs c)
 constexpr int kKnotGroup = 3;
 constexpr int kKnotBlock = 1024;
 
-template <typename GT>
-__global__ __launch_bounds__(kKnotBlock) void knot_grad_kernel(const BwdArgs a)
+template <typename GT, bool SWAPPED>
+__global__ __launch_bounds__(kKnotBlock) void knot_grad_kernel(const BwdArgs a, const BlockLayout y)
 {
-    __shared__ unsigned long long gsl[kKnotGroup][kDmaNodes];
-    __shared__ int khist[kKnotBlock / 64][kDealKeys];
+    // [y.words][kKnotGroup] (the flavours side by side: an add's address serves all of
+    // them, and 16 neighbouring words stay on different banks), then the fold constants
+    extern __shared__ unsigned long long gsl[];
+    FoldPair *const cx = reinterpret_cast<FoldPair *>(gsl + kKnotGroup * y.words);
+    FoldPair *const cq = cx + a.nx - 1;
     __shared__ double wmax[kKnotGroup + 2][kKnotBlock / 64];
     const GT *gout = reinterpret_cast<const GT *>(a.gout);
     const int grp = blockIdx.y;
     const int u0 = grp * kKnotGroup;
     const int nu = a.n_u - u0 < kKnotGroup ? a.n_u - u0 : kKnotGroup;
     const int nx = a.nx, nq = a.nq, nodes = nx * nq;
-    for (int e = threadIdx.x; e < nodes; e += kKnotBlock)
-        for (int j = 0; j < kKnotGroup; ++j)
-            gsl[j][e] = 0ull;
+    for (int e = threadIdx.x; e < kKnotGroup * y.words; e += kKnotBlock)
+        gsl[e] = 0ull;
+    for (int i = threadIdx.x; i < nx - 1; i += kKnotBlock)
+        cx[i] = FoldPair{a.ax.rec64[i].pl, a.ax.rec64[i].pr};
+    for (int i = threadIdx.x; i < nq - 1; i += kKnotBlock)
+        cq[i] = FoldPair{a.aq.rec64[i].pl, a.aq.rec64[i].pr};
     const int64_t p_begin = (int64_t)blockIdx.x * a.chunk;
     const int64_t p_end = p_begin + a.chunk < a.n ? p_begin + a.chunk : a.n;
     int col[kKnotGroup];     // first output column of flavour j (clamped to a valid one)
@@ -325,12 +332,22 @@ __global__ __launch_bounds__(kKnotBlock) void knot_grad_kernel(const BwdArgs a)
         col[j] = a.ucols[a.ucol_off[u]];
         more[j] = j < nu && a.ucol_off[u + 1] - a.ucol_off[u] > 1;
     }
-    // dL/dout of the group's flavours at point p, each summed over its columns
-    // (the first columns loaded together, so that their latencies overlap)
-    auto gsum = [&](int64_t p, double (&g)[kKnotGroup]) {
+    // dL/dout of the group's flavours at point p, each summed over its columns: the
+    // first columns (loaded together, so that their latencies overlap), then the rest
+    struct First {
+        GT v[kKnotGroup];
+    };
+    auto first_cols = [&](int64_t p) {
+        First f;
 #pragma unroll
         for (int j = 0; j < kKnotGroup; ++j)
-            g[j] = (double)gout[p * a.n_req + col[j]];
+            f.v[j] = gout[p * a.n_req + col[j]];
+        return f;
+    };
+    auto gsum = [&](int64_t p, const First &f, double (&g)[kKnotGroup]) {
+#pragma unroll
+        for (int j = 0; j < kKnotGroup; ++j)
+            g[j] = (double)f.v[j];
 #pragma unroll
         for (int j = 0; j < kKnotGroup; ++j)
             if (more[j])
@@ -354,7 +371,7 @@ __global__ __launch_bounds__(kKnotBlock) void knot_grad_kernel(const BwdArgs a)
         for (int64_t p = p_begin + threadIdx.x; p < p_end; p += kKnotBlock) {
             const bool in = !(a.st_flag[p] & kBwdOut);
             double g[kKnotGroup];
-            gsum(p, g);
+            gsum(p, first_cols(p), g);
 #pragma unroll
             for (int j = 0; j < kKnotGroup; ++j) {
                 const double ag = fabs(g[j]);
@@ -401,49 +418,43 @@ __global__ __launch_bounds__(kKnotBlock) void knot_grad_kernel(const BwdArgs a)
         any = any || (j < nu && fin[j]);
         fs[j] = uniform(ldexp(1.0, fin[j] ? fixed_exponent(bnd, p_end - p_begin) : 0));
     }
-    const int lane = threadIdx.x & 63;
-    int *hist = khist[threadIdx.x >> 6];
-    // The keys (state of the lane's point) are loaded a step ahead; the dealt
-    // point's local coordinates and dL/dout are then read at its own index.
-    int kidx, kflag;
-    auto load_key = [&](int64_t p0, int &ki, int &kf) {
-        const int64_t pn = p0 + lane;
-        const int64_t pc = pn < p_end ? (pn > p_begin ? pn : p_begin) : p_end - 1;
-        ki = a.st_idx[pc];
-        kf = a.st_flag[pc];
+    const int key = threadIdx.x & 15;
+    // The next step's state is loaded a step ahead (clamped to the chunk).
+    struct State {
+        int idx, flag;
+        double tx, tq;
+        First f;
     };
-    // wave-uniform loop: every lane takes part in the dealing
-    const int64_t pw = p_begin + (threadIdx.x & ~63);
-    load_key(pw, kidx, kflag);
-    for (int64_t p0 = pw; any && p0 < p_end; p0 += kKnotBlock) {
-        int nidx, nflag;
-        load_key(p0 + kKnotBlock, nidx, nflag);   // unconditional (clamped): no wait covers it
-        const bool valid = p0 + lane < p_end && !(kflag & kBwdOut);
-        int key = kDealKeys - 1;
-        if (valid) {
-            int sx = (kidx & 0xffff) - 1, sq = (kidx >> 16) - 1;
-            sx = sx < 0 ? 0 : (sx > nx - 4 ? nx - 4 : sx);
-            sq = sq < 0 ? 0 : (sq > nq - 4 ? nq - 4 : sq);
-            key = (sx * nq + sq) & 31;
-        }
-        const int src = wave_deal(key, hist);
-        const bool ok = __shfl((int)valid, src) != 0;
-        const int idx = __shfl(kidx, src);
-        kidx = nidx;
-        kflag = nflag;
-        if (!ok)   // outside the grid (NaN mode), NaN input, past the chunk
+    auto load_state = [&](int64_t p) {
+        const int64_t pc = p < p_end ? p : p_end - 1;
+        return State{a.st_idx[pc], a.st_flag[pc], a.st_tx[pc], a.st_tq[pc], first_cols(pc)};
+    };
+    int64_t p = p_begin + threadIdx.x;
+    State nxt = load_state(p);
+    for (; any && p < p_end; p += kKnotBlock) {
+        const State st = nxt;
+        nxt = load_state(p + kKnotBlock);
+        if (st.flag & kBwdOut)   // outside the grid (NaN mode), NaN input
             continue;
-        const int64_t p = p0 + src;
-        const double tx = a.st_tx[p], tq = a.st_tq[p];
+        const double tx = st.tx, tq = st.tq;
         double gv[kKnotGroup];
-        gsum(p, gv);
-        const int ix = idx & 0xffff, kq = idx >> 16;
-        const IntervalRec<double> rx = a.ax.rec64[ix];
-        const IntervalRec<double> rq = a.aq.rec64[kq];
-        double wx[4], wq[4];
-        fwd::fold<double>(tx, rx.pl, rx.plql, rx.ql, rx.qr, rx.qrpr, rx.pr, wx);
-        fwd::fold<double>(tq, rq.pl, rq.plql, rq.ql, rq.qr, rq.qrpr, rq.pr, wq);
-        const int base = fwd::window(ix, nx, wx) * nq + fwd::window(kq, nq, wq);
+        gsum(p, st.f, gv);
+        const int ix = st.idx & 0xffff, kq = st.idx >> 16;
+        double wx[4], wq[4], wa[4], wb[4];
+        fold_pair(tx, cx[ix], wx);
+        fold_pair(tq, cq[kq], wq);
+        const int sx = fwd::window(ix, nx, wx), sq = fwd::window(kq, nq, wq);
+        int row[4], colw[4];
+        visit_weights(SWAPPED ? wq : wx, SWAPPED ? sq : sx, key, wa);
+        visit_weights(SWAPPED ? wx : wq, SWAPPED ? sx : sq, key >> 2, wb);
+        visit_rows<8 * kKnotGroup>(SWAPPED ? sq : sx, y.strip, key, row);
+        visit_cols<8 * kKnotGroup>(SWAPPED ? sx : sq, key, colw);
+        LdsWord *word[4][4];
+#pragma unroll
+        for (int jx = 0; jx < 4; ++jx)
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk)
+                word[jx][kk] = visit_word(gsl, row[jx], colw[kk]);
 #pragma unroll
         for (int j = 0; j < kKnotGroup; ++j) {
             if (j < nu && fin[j]) {
@@ -451,10 +462,10 @@ __global__ __launch_bounds__(kKnotBlock) void knot_grad_kernel(const BwdArgs a)
                 if (fabs(g) < 1.0 / 0.0) {
 #pragma unroll
                     for (int jx = 0; jx < 4; ++jx) {
-                        const double gx = g * wx[jx];
+                        const double gx = g * wa[jx] * fs[j];   // fs: a power of two
 #pragma unroll
                         for (int kk = 0; kk < 4; ++kk)
-                            atomicAdd(&gsl[j][base + jx * nq + kk], to_fixed(gx * wq[kk], fs[j]));
+                            atomicAdd((unsigned long long *)(word[jx][kk] + j), to_fixed(gx, wb[kk]));
                     }
                 } else {
                     // weights of knots ix-1 .. ix+2, kq-1 .. kq+2 (not shifted
@@ -481,15 +492,18 @@ __global__ __launch_bounds__(kKnotBlock) void knot_grad_kernel(const BwdArgs a)
         }
     }
     __syncthreads();
-    for (int j = 0; j < nu; ++j) {
-        double *dst = a.gacc + (size_t)a.urow[u0 + j] * nodes;
-        const double inv = 1.0 / fs[j];   // exact: a power of two
-        for (int e = threadIdx.x; e < nodes; e += kKnotBlock) {
-            const long long v = (long long)gsl[j][e];
+    for (int e = threadIdx.x; e < nodes; e += kKnotBlock) {
+        const int i = e / nq, w = block_word(y, i, e - i * nq);
+#pragma unroll
+        for (int j = 0; j < kKnotGroup; ++j) {
+            if (j >= nu)
+                continue;
+            double *dst = a.gacc + (size_t)a.urow[u0 + j] * nodes;
+            const long long v = (long long)gsl[w * kKnotGroup + j];
             if (!fin[j])
                 unsafeAtomicAdd(&dst[e], __builtin_nan(""));
             else if (v != 0)
-                unsafeAtomicAdd(&dst[e], (double)v * inv);
+                unsafeAtomicAdd(&dst[e], (double)v * (1.0 / fs[j]));   // exact: a power of two
         }
     }
 }
@@ -511,13 +525,25 @@ hipError_t launch_knot_grad(const BwdArgs &b, bool f32, int cus, hipStream_t s)
         chunk = kKnotBlock;
     nchunk = (b.n + chunk - 1) / chunk;
     k.chunk = (int)chunk;
+    // up to 5000 knots take at most 5210 words in the better of the two orders
+    constexpr size_t room = kLdsLimit - (kKnotGroup + 2) * (kKnotBlock / 64) * sizeof(double);
+    const size_t pairs = (size_t)(b.nx + b.nq - 2) * sizeof(FoldPair);
+    const BlockLayout y = block_layout(b.nx, b.nq, (int)((room - pairs) / (8 * kKnotGroup)));
+    const size_t lds = (size_t)kKnotGroup * y.words * 8 + pairs;
+    if (lds > room)
+        return hipErrorInvalidValue;
+    auto go = [&](auto fn) -> hipError_t {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess)
+            return e;
+        hipLaunchKernelGGL(fn, dim3((unsigned)nchunk, (unsigned)ngroups), dim3(kKnotBlock), lds, s,
+                           k, y);
+        return hipGetLastError();
+    };
     if (f32)
-        hipLaunchKernelGGL(knot_grad_kernel<float>, dim3((unsigned)nchunk, (unsigned)ngroups),
-                           dim3(kKnotBlock), 0, s, k);
-    else
-        hipLaunchKernelGGL(knot_grad_kernel<double>, dim3((unsigned)nchunk, (unsigned)ngroups),
-                           dim3(kKnotBlock), 0, s, k);
-    return hipGetLastError();
+        return y.swapped ? go(knot_grad_kernel<float, true>) : go(knot_grad_kernel<float, false>);
+    return y.swapped ? go(knot_grad_kernel<double, true>) : go(knot_grad_kernel<double, false>);
 }
 
 constexpr int kCoordBlock = 512;

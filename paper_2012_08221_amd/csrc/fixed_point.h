@@ -23,11 +23,12 @@ __device__ __forceinline__ double weight_sum_bound(const IntervalRec<double> &r)
 }
 
 // Round-to-nearest fixed point of c * f (|c * f| < 2^51): adding 1.5 * 2^52
-// leaves the integer in the low mantissa bits.
+// leaves the integer in the low mantissa bits.  (The constant's low word is 0:
+// taking it off again is one subtraction from the high word.)
 __device__ __forceinline__ unsigned long long to_fixed(double c, double f)
 {
-    const double t = fma(c, f, 6755399441055744.0);
-    return (unsigned long long)(__double_as_longlong(t) - 0x4338000000000000LL);
+    const unsigned long long t = (unsigned long long)__double_as_longlong(fma(c, f, 6755399441055744.0));
+    return (unsigned long long)((unsigned)(t >> 32) - 0x43380000u) << 32 | (unsigned)t;
 }
 
 // Fixed-point exponent for terms bounded by bnd, summed at most n at a time.

@@ -496,3 +496,43 @@ def test_backward_ragged_sizes(torch, mods, prec_name, n):
         arr = np.array(out)
         assert len(arr) >= 10
         assert metric(arr[:, 0], arr[:, 1]).max() <= TOL
+
+
+@pytest.mark.parametrize("nx,nq", [(4, 4), (7, 5), (21, 18), (100, 50), (5, 1000), (1000, 5)])
+def test_knot_gradient_is_the_adjoint(torch, mods, nx, nq):
+    """sum g xf(v') = sum dL/dv v' for random knot values v', with the oracle's xf: the
+    knot pass at the smallest grids, at sizes that are not multiples of its 4 x 4
+    blocks, at the largest, and at long thin ones (whose blocks run along either axis).
+    4 flavours: a full group and one of a single flavour.  Tolerance: n terms
+    whose rounding errors (1e-15 of the largest |g| |v'| times the weights' sum, under 20
+    here) add up at worst."""
+    api, ag = mods
+    rng = np.random.default_rng(nx * 10007 + nq)
+    sub = nq // 2 if nq >= 12 else nq
+    q2 = np.exp(np.cumsum(rng.uniform(0.02, 0.08, nq)))
+    off = [0, nq]
+    if sub < nq:
+        q2[sub] = q2[sub - 1]
+        off = [0, sub, nq]
+    xk = np.exp(np.cumsum(rng.uniform(0.01, 0.04, nx)))
+    xk *= 0.9 / xk[-1]
+    pids = [1, 2, 3, 21]
+    g = wl.GridSpec(pids=np.array(pids, np.int32), x=xk, q2=q2, q_off=np.array(off, np.int32),
+                    xf=rng.standard_normal((4, nx, nq)))
+    pdf = api.mkPDF(g, with_values=False)
+    n = 5000
+    x = np.exp(rng.uniform(math.log(xk[0]), math.log(xk[-1]), n))
+    q = np.exp(rng.uniform(math.log(q2[0]), math.log(q2[-1]), n))
+    x[:4], q[:4] = xk[[0, -1, 0, -1]], q2[[0, -1, -1, 0]]
+    gout = rng.uniform(-1, 1, (n, 4))
+    v = torch.as_tensor(g.xf, device="cuda").requires_grad_(True)
+    out = ag.xfx(pdf, v, pids, torch.as_tensor(x, device="cuda"),
+                 torch.as_tensor(q, device="cuda"), prec="f64")
+    (gv,) = torch.autograd.grad(out, v, torch.as_tensor(gout, device="cuda"))
+    gv = gv.cpu().numpy()
+    for _ in range(2):
+        vals = rng.standard_normal((4, nx, nq))
+        gp = wl.GridSpec(pids=g.pids, x=g.x, q2=g.q2, q_off=g.q_off, xf=vals)
+        want = (gout * oracle.xfx(gp, pids, x, q)).sum(axis=0)
+        got = (gv * vals).sum(axis=(1, 2))
+        assert np.all(np.abs(got - want) <= n * 1e-15 * 20 * np.abs(vals).max()), (got, want)
