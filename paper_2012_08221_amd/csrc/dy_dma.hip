@@ -16,6 +16,7 @@
 // read from global memory.
 #include "xfx_dma_impl.h"
 #include "fixed_point.h"
+#include "scatter_order.h"
 
 namespace pdfx {
 
@@ -309,16 +310,19 @@ hipError_t dy_dma_typed(const DyArgs &a, LaunchShape ls, int cus, hipStream_t s,
 // dI/dv_q[i][k]  = L^2 alpha_s xf_-q(x2) w1_i wq_k and
 // dI/dv_-q[i][k] = L^2 alpha_s xf_q(x1)  w2_i wq_k, summed over the points.
 // A workgroup takes one pair (q, -q) and one chunk of points: both value
-// slabs and both FP64 gradient slabs (borderless) sit in LDS, so each point's
+// slabs and both gradient slabs (borderless) sit in LDS, so each point's
 // state (bins, local coordinates, alpha_s from the state pass) is read and its
 // weights folded once for the two flavours, and each partner value comes from
 // a 16-tap stencil of the other flavour's slab.  The LDS gradients are added
-// to the FP64 accumulator at the end.  The scatter is bound by LDS atomics:
-// each wave deals its points out to lanes by the bank of the quark stencil's
-// base (wave_deal), which spreads the quark half of the adds over the banks,
-// and the sums are kept in 64-bit fixed point (integer LDS adds run ~1.9x
-// faster than FP64 ones, and integer sums are exact and independent of the
-// order of the adds).  The scale is a power of two per workgroup and array,
+// to the FP64 accumulator at the end.  The 32 adds of a point are made in its lane's
+// own order over a blocked layout (scatter_order.h), so that the lanes of an add hit
+// different banks, and so are its 32 reads (the stencil sums of a point then depend on
+// its lane in the last bit); the constants that the weights need are in LDS.  The sums
+// are kept in 64-bit fixed point (integer LDS adds run ~1.9x faster than FP64 ones, and
+// integer sums are exact and independent of the order of the adds).  1e7 points, 100 x
+// 50 knots, FP64: 870 us, 620 of them vector instructions and 433 LDS; in one order, with
+// the points dealt to lanes by the bank of the quark's stencil and the interval records
+// gathered from global memory, 1076 us (926 of them LDS).  The scale is a power of two per workgroup and array,
 // from a bound on the terms: |alpha_s| <= B_a max|alpha knot|, a partner value
 // <= B_x B_q max|row value|, one weight product <= B_x B_q, with B the largest
 // sum of |weights| over an axis' intervals (1 + 4/27 times the sum of the
@@ -327,18 +331,33 @@ hipError_t dy_dma_typed(const DyArgs &a, LaunchShape ls, int cus, hipStream_t s,
 // Non-finite inputs make the two rows' gradients NaN.
 
 constexpr int kPairBlock = 1024;
+// Where the pair's knots lie: the quark's in strips of 4 lines upwards from word 0, the
+// antiquark's in strips downwards from `down`.  If the last strip holds 1 or 2 lines,
+// the two flavours' share its words, so that 100 x 50 FP64 knots fit with strips of a
+// multiple of 16 words (BlockLayout; else windows across two strips meet other lanes'
+// words: the kernel's LDS time 671 us instead of 433 at 1e7 points).
+struct PairLayout {
+    int strip, down, words;   // words: of both flavours
+    bool swapped;             // strips along Q^2 instead of x
+    bool pairs;               // the intervals' FoldPair fit, too
+};
 
+__device__ __forceinline__ int pair_word(const PairLayout &y, bool anti, int ix, int kq)
+{
+    const int a = y.swapped ? kq : ix, b = y.swapped ? ix : kq;
+    return (anti ? y.down - (a >> 2) * y.strip : (a >> 2) * y.strip) + b * 4 + (a & 3);
+}
 
-template <typename V>
-__global__ __launch_bounds__(kPairBlock) void dy_pair_adjoint_kernel(const DyArgs a)
+// LDS: the gradients of the two flavours, then their values in the same layout (FP32
+// ones widened), then the FoldPair of the intervals of the x axis and of the Q^2 axis.
+template <typename V, bool SWAPPED>
+__global__ __launch_bounds__(kPairBlock) void dy_pair_adjoint_kernel(const DyArgs a, const PairLayout y)
 {
     constexpr int G = 16 / (int)sizeof(V);
-    __shared__ V vq[kDmaNodes];
-    __shared__ V vqb[kDmaNodes];
-    __shared__ unsigned long long gq[kDmaNodes];
-    __shared__ unsigned long long gqb[kDmaNodes];
-    __shared__ int khist[kPairBlock / 64][kDealKeys];
-    __shared__ double wmax[6][kPairBlock / 64];
+    extern __shared__ unsigned long long gq[];
+    double *const vals = reinterpret_cast<double *>(gq + y.words);
+    FoldPair *const cx = reinterpret_cast<FoldPair *>(gq + 2 * y.words);
+    FoldPair *const cq = cx + a.nx - 1;
     const int q = blockIdx.y + 1;          // quark q: row 5 + q; antiquark: row 5 - q
     const int rq = 5 + q, rqb = 5 - q;
     const int nx = a.nx, nq = a.nq, nodes = nx * nq;
@@ -347,38 +366,53 @@ __global__ __launch_bounds__(kPairBlock) void dy_pair_adjoint_kernel(const DyArg
     // the x, Q^2 and alpha_s axes, max |alpha_s knot value|
     double m[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     for (int e = threadIdx.x; e < nodes; e += kPairBlock) {
-        vq[e] = src[((size_t)(rq / G) * a.gstride + e) * G + rq % G];
-        vqb[e] = src[((size_t)(rqb / G) * a.gstride + e) * G + rqb % G];
-        m[0] = nan_max(m[0], fabs((double)vq[e]));
-        m[1] = nan_max(m[1], fabs((double)vqb[e]));
-        gq[e] = 0ull;
-        gqb[e] = 0ull;
+        const V u = src[((size_t)(rq / G) * a.gstride + e) * G + rq % G];
+        const V ub = src[((size_t)(rqb / G) * a.gstride + e) * G + rqb % G];
+        const int i = e / nq, k = e - i * nq;
+        vals[pair_word(y, false, i, k)] = (double)u;
+        vals[pair_word(y, true, i, k)] = (double)ub;
+        m[0] = nan_max(m[0], fabs((double)u));
+        m[1] = nan_max(m[1], fabs((double)ub));
     }
-    for (int i = threadIdx.x; i < nx - 1; i += kPairBlock)
-        m[2] = fmax(m[2], weight_sum_bound(a.ax.rec64[i]));
-    for (int i = threadIdx.x; i < nq - 1; i += kPairBlock)
-        m[3] = fmax(m[3], weight_sum_bound(a.aq.rec64[i]));
+    for (int i = threadIdx.x; i < nx - 1; i += kPairBlock) {
+        const IntervalRec<double> r = a.ax.rec64[i];
+        m[2] = fmax(m[2], weight_sum_bound(r));
+        if (y.pairs)
+            cx[i] = FoldPair{r.pl, r.pr};
+    }
+    for (int i = threadIdx.x; i < nq - 1; i += kPairBlock) {
+        const IntervalRec<double> r = a.aq.rec64[i];
+        m[3] = fmax(m[3], weight_sum_bound(r));
+        if (y.pairs)
+            cq[i] = FoldPair{r.pl, r.pr};
+    }
     for (int i = threadIdx.x; i < a.aa.n - 1; i += kPairBlock)
         m[4] = fmax(m[4], weight_sum_bound(a.aa.rec64[i]));
     for (int i = threadIdx.x; i < a.aa.n + 2; i += kPairBlock)
         m[5] = fmax(m[5], fabs(a.as_vals64[i]));
+    // the waves' maxima meet in the gradients' place
+    double *const wmax = reinterpret_cast<double *>(gq);
 #pragma unroll
     for (int j = 0; j < 6; ++j) {
         double v = m[j];
 #pragma unroll
-        for (int d = 1; d < 64; d <<= 1)
-            v = nan_max(v, __shfl_xor(v, d));
+        for (int k = 1; k < 64; k <<= 1)
+            v = nan_max(v, __shfl_xor(v, k));
         if ((threadIdx.x & 63) == 0)
-            wmax[j][threadIdx.x >> 6] = v;
+            wmax[j * (kPairBlock / 64) + (threadIdx.x >> 6)] = v;
     }
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < 6; ++j) {
-        double v = wmax[j][0];
+        double v = wmax[j * (kPairBlock / 64)];
         for (int w = 1; w < kPairBlock / 64; ++w)
-            v = nan_max(v, wmax[j][w]);
+            v = nan_max(v, wmax[j * (kPairBlock / 64) + w]);
         m[j] = v;
     }
+    __syncthreads();
+    for (int e = threadIdx.x; e < y.words; e += kPairBlock)
+        gq[e] = 0ull;
+    __syncthreads();
     const int64_t p_begin = (int64_t)blockIdx.x * a.chunk;
     const int64_t p_end = p_begin + a.chunk < a.n ? p_begin + a.chunk : a.n;
     // quark terms carry the antiquark value and the reverse
@@ -388,72 +422,89 @@ __global__ __launch_bounds__(kPairBlock) void dy_pair_adjoint_kernel(const DyArg
     const int e_q = finite ? fixed_exponent(bnd_q, p_end - p_begin) : 0;
     const int e_qb = finite ? fixed_exponent(bnd_qb, p_end - p_begin) : 0;
     const double f_q = ldexp(1.0, e_q), f_qb = ldexp(1.0, e_qb);
-    const int lane = threadIdx.x & 63;
-    int *hist = khist[threadIdx.x >> 6];
-    // The keys (each lane's quark bins) are loaded one wave step ahead; the
-    // dealt point's state is then read at its own index, all at once.
-    auto load_key = [&](int64_t p0) {
-        const int64_t pn = p0 + lane;
-        return a.st_i1[pn < p_end ? (pn > p_begin ? pn : p_begin) : p_end - 1];
+    const int key = threadIdx.x & 15;
+    // The next step's state is loaded a step ahead (clamped to the chunk).
+    struct State {
+        int i1, i2;
+        double t1, t2, tq, as;
     };
-    // wave-uniform loop: every lane takes part in the dealing
-    const int64_t pw = p_begin + (threadIdx.x & ~63);
-    int kidx = load_key(pw);
-    for (int64_t p0 = pw; finite && p0 < p_end; p0 += kPairBlock) {
-        const int nidx = load_key(p0 + kPairBlock);   // unconditional (clamped): no wait covers it
-        const bool valid = p0 + lane < p_end && kidx >= 0;
-        int key = kDealKeys - 1;
-        if (valid) {
-            int sx = (kidx & 0xffff) - 1, sq = (kidx >> 16) - 1;
-            sx = sx < 0 ? 0 : (sx > nx - 4 ? nx - 4 : sx);
-            sq = sq < 0 ? 0 : (sq > nq - 4 ? nq - 4 : sq);
-            key = (sx * nq + sq) & 31;
-        }
-        const int src = wave_deal(key, hist);
-        const bool ok = __shfl((int)valid, src) != 0;
-        const int idx1 = __shfl(kidx, src);
-        kidx = nidx;
-        if (!ok)   // outside the grid, or past the chunk
+    auto load_state = [&](int64_t p) {
+        const int64_t pc = p < p_end ? p : p_end - 1;
+        return State{a.st_i1[pc], a.st_i2[pc], a.st_t1[pc], a.st_t2[pc], a.st_tq[pc], a.st_as[pc]};
+    };
+    int64_t p = p_begin + threadIdx.x;
+    State nxt = load_state(p);
+    for (; finite && p < p_end; p += kPairBlock) {
+        const State st = nxt;
+        nxt = load_state(p + kPairBlock);
+        if (st.i1 < 0)   // outside the grid
             continue;
-        const int64_t p = p0 + src;
-        const int i1 = idx1 & 0xffff, kq = idx1 >> 16, i2 = a.st_i2[p];
-        const double t1 = a.st_t1[p], t2 = a.st_t2[p], tq = a.st_tq[p], as = a.st_as[p];
+        const int i1 = st.i1 & 0xffff, kq = st.i1 >> 16, i2 = st.i2;
+        FoldPair c1, c2, cc;
+        if (y.pairs) {
+            c1 = cx[i1];
+            c2 = cx[i2];
+            cc = cq[kq];
+        } else {
+            c1 = FoldPair{a.ax.rec64[i1].pl, a.ax.rec64[i1].pr};
+            c2 = FoldPair{a.ax.rec64[i2].pl, a.ax.rec64[i2].pr};
+            cc = FoldPair{a.aq.rec64[kq].pl, a.aq.rec64[kq].pr};
+        }
         double w1[4], w2[4], wq[4];
-        {
-            const IntervalRec<double> r1 = a.ax.rec64[i1];
-            const IntervalRec<double> r2 = a.ax.rec64[i2];
-            const IntervalRec<double> rr = a.aq.rec64[kq];
-            fwd::fold<double>(t1, r1.pl, r1.plql, r1.ql, r1.qr, r1.qrpr, r1.pr, w1);
-            fwd::fold<double>(t2, r2.pl, r2.plql, r2.ql, r2.qr, r2.qrpr, r2.pr, w2);
-            fwd::fold<double>(tq, rr.pl, rr.plql, rr.ql, rr.qr, rr.qrpr, rr.pr, wq);
+        fold_pair(st.t1, c1, w1);
+        fold_pair(st.t2, c2, w2);
+        fold_pair(st.tq, cc, wq);
+        const int sq = fwd::window(kq, nq, wq);
+        const int s1 = fwd::window(i1, nx, w1), s2 = fwd::window(i2, nx, w2);
+        // everything below in the lane's order: u[i] the weights along x, uq[k] along Q^2
+        double u1[4], u2[4], uq[4];
+        int l1[4], l2[4], lq1[4], lq2[4];
+        if constexpr (SWAPPED) {
+            visit_weights(wq, sq, key, uq);
+            visit_weights(w1, s1, key >> 2, u1);
+            visit_weights(w2, s2, key >> 2, u2);
+            visit_rows<8>(sq, y.strip, key, lq1);
+            visit_rows<8>(sq, -y.strip, key, lq2);
+            visit_cols<8>(s1, key, l1);
+            visit_cols<8>(s2, key, l2);
+        } else {
+            visit_weights(wq, sq, key >> 2, uq);
+            visit_weights(w1, s1, key, u1);
+            visit_weights(w2, s2, key, u2);
+            visit_rows<8>(s1, y.strip, key, l1);
+            visit_rows<8>(s2, -y.strip, key, l2);
+            visit_cols<8>(sq, key, lq1);
+            visit_cols<8>(sq, key, lq2);
         }
-        const int cq = fwd::window(kq, nq, wq);
-        const int b1 = fwd::window(i1, nx, w1) * nq + cq;
-        const int b2 = fwd::window(i2, nx, w2) * nq + cq;
         // partner values: xf_q(x1) for the antiquark, xf_-q(x2) for the quark
-        double f1 = 0.0, f2 = 0.0;
+        auto partner = [&](int first, const int (&l)[4], const int (&lq)[4], const double (&u)[4]) {
+            double f = 0.0;
 #pragma unroll
-        for (int jx = 0; jx < 4; ++jx) {
-            double r1 = 0.0, r2 = 0.0;
+            for (int i = 0; i < 4; ++i) {
+                double r = 0.0;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                r1 = fma(wq[k], (double)vq[b1 + jx * nq + k], r1);
-                r2 = fma(wq[k], (double)vqb[b2 + jx * nq + k], r2);
+                for (int k = 0; k < 4; ++k)
+                    r = fma(uq[k], __longlong_as_double((long long)*visit_word(gq + first, l[i], lq[k])), r);
+                f = fma(u[i], r, f);
             }
-            f1 = fma(w1[jx], r1, f1);
-            f2 = fma(w2[jx], r2, f2);
-        }
-        const double c = a.scale * a.L2 * as;
-        const double mq = c * f2, mqb = c * f1;
+            return f;
+        };
+        auto scatter = [&](int first, const int (&l)[4], const int (&lq)[4], const double (&u)[4],
+                           double m) {
 #pragma unroll
-        for (int jx = 0; jx < 4; ++jx) {
-            const double m1 = mq * w1[jx], m2 = mqb * w2[jx];
+            for (int i = 0; i < 4; ++i) {
+                const double mi = m * u[i];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                atomicAdd(&gq[b1 + jx * nq + k], to_fixed(m1 * wq[k], f_q));
-                atomicAdd(&gqb[b2 + jx * nq + k], to_fixed(m2 * wq[k], f_qb));
+                for (int k = 0; k < 4; ++k)
+                    atomicAdd((unsigned long long *)visit_word(gq + first, l[i], lq[k]),
+                              to_fixed(mi, uq[k]));
             }
-        }
+        };
+        const double c = a.scale * a.L2 * st.as;
+        const double mq = c * partner(y.words + y.down, l2, lq2, u2) * f_q;   // f_*: powers of two
+        const double mqb = c * partner(y.words, l1, lq1, u1) * f_qb;
+        scatter(0, l1, lq1, u1, mq);
+        scatter(y.down, l2, lq2, u2, mqb);
     }
     __syncthreads();
     double *dq = a.gacc + (size_t)rq * nodes;
@@ -465,7 +516,9 @@ __global__ __launch_bounds__(kPairBlock) void dy_pair_adjoint_kernel(const DyArg
             unsafeAtomicAdd(&dqb[e], __builtin_nan(""));
             continue;
         }
-        const long long sq = (long long)gq[e], sqb = (long long)gqb[e];
+        const int i = e / nq, k = e - i * nq;
+        const long long sq = (long long)gq[pair_word(y, false, i, k)];
+        const long long sqb = (long long)gq[pair_word(y, true, i, k)];
         if (sq != 0)
             unsafeAtomicAdd(&dq[e], (double)sq * i_q);
         if (sqb != 0)
@@ -474,6 +527,28 @@ __global__ __launch_bounds__(kPairBlock) void dy_pair_adjoint_kernel(const DyArg
 }
 
 }  // namespace
+
+// The first that fits: with the constants in LDS, then strips of a multiple of 16 words,
+// then strips along x.  Without any of them every grid of launch_dy_dma_forward fits.
+static bool pair_layout(int nx, int nq, PairLayout *y)
+{
+    auto up = [](int n) { return (n + 3) / 4 * 4; };
+    const int room = (int)(kLdsLimit / 16), pairs = nx + nq - 2;   // in 16 bytes
+    for (int t = 0; t < 8; ++t) {
+        const bool swapped = t & 1, packed = t & 2, far = t & 4;
+        const int na = swapped ? nq : nx, nb = swapped ? nx : nq;
+        const int strips = up(na) / 4, rest = na % 4;
+        const int strip = 4 * (packed ? nb : up(nb));
+        const int down = rest == 1 || rest == 2 ? 2 * (strips - 1) * strip + 2 : (2 * strips - 1) * strip;
+        const int least = 6 * (kPairBlock / 64);   // the waves' maxima
+        const int words = down + strip < least ? least : up(down + strip);
+        if (words + (far ? 0 : pairs) <= room) {
+            *y = PairLayout{strip, down, words, swapped, !far};
+            return true;
+        }
+    }
+    return false;
+}
 
 // Pair-wise integrand adjoint (standard parton order, grid fits the
 // double-buffered layout): one workgroup per (point chunk, q), one resident
@@ -487,9 +562,21 @@ hipError_t launch_dy_pair_adjoint(const DyArgs &a0, bool f32, int cus, hipStream
         chunk = kPairBlock;
     nchunk = (a.n + chunk - 1) / chunk;
     a.chunk = (int)chunk;
-    auto fn = f32 ? dy_pair_adjoint_kernel<float> : dy_pair_adjoint_kernel<double>;
-    hipLaunchKernelGGL(fn, dim3((unsigned)nchunk, 5u), dim3(kPairBlock), 0, s, a);
-    return hipGetLastError();
+    PairLayout y;
+    if (!pair_layout(a.nx, a.nq, &y))
+        return hipErrorInvalidValue;
+    const size_t lds = (size_t)16 * y.words + (y.pairs ? (size_t)(a.nx + a.nq - 2) * sizeof(FoldPair) : 0);
+    auto go = [&](auto fn) -> hipError_t {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess)
+            return e;
+        hipLaunchKernelGGL(fn, dim3((unsigned)nchunk, 5u), dim3(kPairBlock), lds, s, a, y);
+        return hipGetLastError();
+    };
+    if (f32)
+        return y.swapped ? go(dy_pair_adjoint_kernel<float, true>) : go(dy_pair_adjoint_kernel<float, false>);
+    return y.swapped ? go(dy_pair_adjoint_kernel<double, true>) : go(dy_pair_adjoint_kernel<double, false>);
 }
 
 bool dy_shape_supported(LaunchShape ls, bool f32)

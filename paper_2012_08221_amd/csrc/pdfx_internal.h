@@ -36,41 +36,6 @@ __device__ __forceinline__ double load_point(const double *v, int64_t p, int64_t
     return v[p < n ? p : n - 1];
 }
 
-// Keys of the in-wave dealing below: 32 LDS bank keys of an 8-byte word
-// (its index mod 32) and one for lanes that do no work.
-constexpr int kDealKeys = 33;
-
-// In-wave dealing for LDS atomic scatters, which run ~2.7x faster when the
-// lanes of one instruction hit different banks: the 64 lanes' keys (in
-// [0, kDealKeys), the last for idle lanes) are counting-sorted and sorted rank
-// r goes to lane (r mod 4) * 16 + r / 4, so that every 16 lanes hold keys
-// spread over the sorted order.  Returns the lane whose item this lane takes.
-// hist: this wave's kDealKeys ints of LDS.  Every lane of the wave must call
-// it together.
-__device__ __forceinline__ int wave_deal(int key, int *hist)
-{
-    const int lane = threadIdx.x & 63;
-    if (lane < kDealKeys)
-        hist[lane] = 0;
-    __builtin_amdgcn_wave_barrier();
-    const int lrank = atomicAdd(&hist[key], 1);   // rank among the wave's equal keys
-    __builtin_amdgcn_wave_barrier();
-    const int cnt = lane < kDealKeys ? hist[lane] : 0;
-    // inclusive scan over the 64 lanes by DPP (VALU only, leaving the LDS pipe
-    // to the scatter): shifts within each 16-lane row, then the last lane of
-    // row 0 (of row 2) added to row 1 (row 3), then lane 31 to rows 2 and 3
-    int incl = cnt;
-    incl += __builtin_amdgcn_update_dpp(0, incl, 0x111, 0xf, 0xf, true);   // row_shr:1
-    incl += __builtin_amdgcn_update_dpp(0, incl, 0x112, 0xf, 0xf, true);   // row_shr:2
-    incl += __builtin_amdgcn_update_dpp(0, incl, 0x114, 0xf, 0xf, true);   // row_shr:4
-    incl += __builtin_amdgcn_update_dpp(0, incl, 0x118, 0xf, 0xf, true);   // row_shr:8
-    incl += __builtin_amdgcn_update_dpp(0, incl, 0x142, 0xa, 0xf, false);  // row_bcast:15
-    incl += __builtin_amdgcn_update_dpp(0, incl, 0x143, 0xc, 0xf, false);  // row_bcast:31
-    const int rank = __shfl(incl - cnt, key) + lrank;
-    const int dest = (rank & 3) * 16 + (rank >> 2);
-    return __builtin_amdgcn_ds_permute(dest * 4, lane);
-}
-
 // Device view of one axis (global-memory tables).
 struct AxisDev {
     const double *knots;          // raw knots, non-decreasing (search on raw values)

@@ -231,3 +231,35 @@ def test_integrand_backward_scale_range_and_nan(pdf, api, torch, prec):
     for p in (1, 2, 3, 4, 5, -1, -2, -3, -4, -5):
         assert np.isnan(gn[rows[p]]).all()
     assert np.all(gn[rows[21]] == 0.0)
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32s"])
+@pytest.mark.parametrize("nx,nq", [(4, 4), (9, 6), (100, 50), (50, 100), (71, 70), (81, 61),
+                                   (27, 185), (98, 51)])
+def test_gradient_is_the_directional_derivative(api, torch, nx, nq, prec):
+    """sum I(v + h) - sum I(v - h) = 2 dI/dv h, exactly, I being quadratic in the knots:
+    random values and random h, with the oracle's I, on the smallest grid, on sizes with
+    0 to 3 lines in the last block of either axis, and on the largest.  Tolerance:
+    FP64 rounding of n terms of 80 products each against the sum of their sizes; in
+    FP32 the gradient's own rounding (2^-24 of each entry)."""
+    rng = np.random.default_rng(1000 * nx + nq)
+    x = np.exp(np.linspace(math.log(XMIN), 0.0, nx))
+    q2 = np.exp(np.linspace(math.log(3.0), math.log(S), nq))
+    base = cfg0_grid()
+    vals = rng.uniform(0.5, 1.5, (len(base.pids), nx, nq)).astype(np.float32).astype(float)
+
+    def spec(xf):
+        return wl.GridSpec(pids=base.pids, x=x, q2=q2, q_off=np.array([0, nq], np.int32), xf=xf,
+                           as_q2=base.as_q2, as_val=base.as_val)
+
+    pdf = api.mkPDF(spec(vals))
+    u1, u2 = wl.dy_uniforms(3, 3000)
+    dt = torch.float64 if prec == "f64" else torch.float32
+    grad = torch.zeros(pdf.shape, dtype=dt, device="cuda")
+    api.dy_backward(pdf, u1, u2, grad, XMIN, S, prec=prec)
+    grad = grad.double().cpu().numpy()
+    h = rng.uniform(-0.5, 0.5, vals.shape)
+    up, dn = (oracle.dy(spec(vals + f * h), u1, u2, XMIN, S) for f in (1, -1))
+    size = np.abs(up).sum() + np.abs(dn).sum()
+    tol = 1e-12 * size + (0 if prec == "f64" else 2.0 ** -24 * 2 * np.abs(grad * h).sum())
+    assert abs((up - dn).sum() - 2 * (grad * h).sum()) <= tol
