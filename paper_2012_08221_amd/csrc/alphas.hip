@@ -48,7 +48,7 @@ __global__ __launch_bounds__(kAsBlock) void alphas_kernel(const AlphasArgs a, Ax
                 }
             }
             fwd::count_flagged(live && !ok, a.dom_count);
-            const double lq = log(qv);
+            const double lq = ln(qv);
             const int k = fwd::lbin(la, qv, lq);
             V w[4];
             fwd::weights<V>(la, k, lq, w);

@@ -84,7 +84,7 @@ __global__ __launch_bounds__(kStateBlock) void state_kernel(const BwdArgs a)
             xv = a.ax.lo;
             qv = a.aq.lo;
         }
-        const double lnx = log(xv), lnq = log(qv);
+        const double lnx = ln(xv), lnq = ln(qv);
         const int ix = fwd::lbin(lx, xv, lnx);
         const int kq = fwd::lbin(lq, qv, lnq);
         a.st_idx[p] = ix | (kq << 16);

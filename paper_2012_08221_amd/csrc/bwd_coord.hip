@@ -156,7 +156,7 @@ __global__ __launch_bounds__(BLOCK) void coord_grad_kernel(const CoordArgs c)
                                           : kBwdOut;
         }
         fwd::domain(a, xv, qv);
-        const double lnx = log(xv), lnq = log(qv);
+        const double lnx = ln(xv), lnq = ln(qv);
         const int ix = fwd::lbin(lx, xv, lnx);
         const int kq = fwd::lbin(lq, qv, lnq);
         const IntervalRec<double> rx = a.ax.rec64[ix];

@@ -95,7 +95,7 @@ __global__ __launch_bounds__(BLOCK) void dy_kernel(const DyArgs a)
                 lnx1 = lnx2 = a.ax.ln_lo;
                 q2 = a.aq.lo > a.aa.lo ? a.aq.lo : a.aa.lo;
             }
-            const double lnq = log(q2);
+            const double lnq = ln(q2);
             const int i1 = fwd::lbin(lx, x1, lnx1);
             const int i2 = fwd::lbin(lx, x2, lnx2);
             const int kq = fwd::lbin(lq, q2, lnq);
@@ -235,7 +235,7 @@ __global__ __launch_bounds__(256) void dy_state_kernel(const DyArgs a)
             lnx1 = lnx2 = a.ax.ln_lo;
             q2 = a.aq.lo > a.aa.lo ? a.aq.lo : a.aa.lo;
         }
-        const double lnq = log(q2);
+        const double lnq = ln(q2);
         const int i1 = fwd::lbin(lx, x1, lnx1);
         const int i2 = fwd::lbin(lx, x2, lnx2);
         const int kq = fwd::lbin(lq, q2, lnq);

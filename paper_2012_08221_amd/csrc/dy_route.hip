@@ -289,7 +289,7 @@ __global__ __launch_bounds__(kDyRouteBlock) void dy_route_kernel(const DyRouteAr
         double x1, x2, q2, l1, l2;
         const bool ok = place_point(ua, ub, x1, x2, q2, l1, l2);
         fwd::count_flagged(live && !ok, a.dom_count);
-        const double lnq = log(q2);
+        const double lnq = ln(q2);
         V w1[4], w2[4], wq[4];
         const int i1 = piece_bin(px, x1, l1), i2 = piece_bin(px, x2, l2);
         const int kq = piece_bin(pq, q2, lnq);
@@ -327,7 +327,7 @@ __global__ __launch_bounds__(kDyRouteBlock) void dy_route_kernel(const DyRouteAr
             const bool ok = place_point(ua, ub, x1, x2, q2, l1, l2);
             if (!ok)   // only some lanes are here
                 atomicAdd(a.dom_count, 1ull);
-            const double lnq = log(q2);
+            const double lnq = ln(q2);
             V w1[4], w2[4], wq[4];
             const int s1 = window4(far_weights<V>(a.ax, x1, l1, w1), nx, w1);
             const int s2 = window4(far_weights<V>(a.ax, x2, l2, w2), nx, w2);

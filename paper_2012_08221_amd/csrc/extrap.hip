@@ -102,11 +102,11 @@ __device__ void continue_column(const ExtrapArgs &a, int64_t p, int r)
         double w[4] = {0.0, 0.0, 0.0, 0.0};
         int bin = 0;
         if (!qo) {
-            const double lq = log(qv);
+            const double lq = ln(qv);
             bin = seeded_bin(a.aq, qv, lq);
             weights64(a.aq, bin, qv, lq, w);
         } else if (!xo) {
-            const double lx = log(xv);
+            const double lx = ln(xv);
             bin = seeded_bin(a.ax, xv, lx);
             weights64(a.ax, bin, xv, lx, w);
         }

@@ -99,7 +99,7 @@ __global__ __launch_bounds__(BLOCK) void lumi_kernel(const LumiArgs a)
         q_in = q2 >= a.aq.lo && q2 <= a.aq.hi;
         if (!q_in)
             q2 = a.domain_mode == 1 ? fmin(fmax(q2, a.aq.lo), a.aq.hi) : a.aq.lo;
-        const double lnq = log(q2);
+        const double lnq = ln(q2);
         const int kq = fwd::lbin(lq, q2, lnq);
         fwd::weights_gmem<V>(a.aq, kq, lnq, wqf);
         cqf = fwd::window(kq, nq, wqf);
@@ -123,7 +123,7 @@ __global__ __launch_bounds__(BLOCK) void lumi_kernel(const LumiArgs a)
                 }
             }
             fwd::count_flagged(p < a.n && !st.ok, a.dom_count);
-            const double lnx1 = log(x1), lnx2 = log(x2);
+            const double lnx1 = ln(x1), lnx2 = ln(x2);
             const int i1 = fwd::lbin(lx, x1, lnx1);
             const int i2 = fwd::lbin(lx, x2, lnx2);
             fwd::weights_gmem<V>(a.ax, i1, lnx1, st.w1);
@@ -149,7 +149,7 @@ __global__ __launch_bounds__(BLOCK) void lumi_kernel(const LumiArgs a)
             }
         }
         fwd::count_flagged(p < a.n && !st.ok, a.dom_count);
-        const double lnx1 = log(x1), lnx2 = log(x2), lnq = log(q2);
+        const double lnx1 = ln(x1), lnx2 = ln(x2), lnq = ln(q2);
         const int i1 = fwd::lbin(lx, x1, lnx1);
         const int i2 = fwd::lbin(lx, x2, lnx2);
         const int kq = fwd::lbin(lq, q2, lnq);

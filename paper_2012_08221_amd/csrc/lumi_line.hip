@@ -50,7 +50,7 @@ __global__ __launch_bounds__(kLineBlock) void lumi_line_kernel(const LumiLineArg
     if (!q_in)
         q2 = a.domain_mode == 1 ? fmin(fmax(q2, a.aq.lo), a.aq.hi) : a.aq.lo;
     V wq[4];
-    const double lnq = log(q2);
+    const double lnq = ln(q2);
     const int cq = window4(far_weights<V>(a.aq, q2, lnq, wq), nq, wq);
     const V *const src = reinterpret_cast<const V *>(a.vals);
     for (int e = tid; e < a.n_row * nx; e += kLineBlock) {
@@ -88,7 +88,7 @@ __global__ __launch_bounds__(kLineBlock) void lumi_line_kernel(const LumiLineArg
         }
         const bool live = p < a.n;
         fwd::count_flagged(live && !ok, a.dom_count);
-        const double ln1 = log(x1), ln2 = log(x2);
+        const double ln1 = ln(x1), ln2 = ln(x2);
         V w1[4], w2[4];
         int i1 = piece_bin(px, x1, ln1), i2 = piece_bin(px, x2, ln2);
         piece_weights<V>(px, i1, ln1, w1);

@@ -97,7 +97,7 @@ __global__ __launch_bounds__(BLOCK) void set_kernel(const SetArgs a)
                     }
                 }
                 fwd::count_flagged(live[j] && !ok[j], a.dom_count);
-                const double lnx = log(xv), lnq = log(qv);
+                const double lnx = ln(xv), lnq = ln(qv);
                 const int ix = fwd::lbin(lx, xv, lnx);
                 const int kq = fwd::lbin(lq, qv, lnq);
                 fwd::weights<V>(lx, ix, lnx, wx[j]);

@@ -192,7 +192,7 @@ __device__ __forceinline__ void set_item(const SetDmaArgs &a, const SetPlan &pl,
                 }
             }
             fwd::count_flagged(p < a.n && !ok[j], a.dom_count);
-            const double lnx = log(xv), lnq = log(qv);
+            const double lnx = ln(xv), lnq = ln(qv);
             const int ix = fwd::lbin(lx, xv, lnx);
             const int kq = fwd::lbin(lq, qv, lnq);
             weights_g<V>(md.ax, ix, lnx, wx[j]);

@@ -70,7 +70,7 @@ __global__ __launch_bounds__(64 * kGrpMaxSlots / 2) void xfx_direct_kernel(const
         if constexpr (AS)
             fwd::count_flagged(live && !q_ok, a.dom_count);
     }
-    const double lnx = log(xv), lnq = log(qv);
+    const double lnx = ln(xv), lnq = ln(qv);
     V wx[4], wq[4];
     const int ix = piece_bin(px, xv, lnx), kq = piece_bin(pq, qv, lnq);
     piece_weights<V>(px, ix, lnx, wx);

@@ -227,8 +227,8 @@ __global__ __launch_bounds__(BLOCK) void xfx_dma_kernel(const XfxArgs a)
         count_flagged(p < a.n && !ook, a.dom_count);
         if constexpr (AS)
             count_flagged(p < a.n && !q_ok, a.dom_count);
-        const double lnx = log(xv);
-        const double lnq = log(qv);
+        const double lnx = ln(xv);
+        const double lnq = ln(qv);
         const int ix = lbin(lx, xv, lnx);
         const int kq = lbin(lq, qv, lnq);
         weights_gmem<V>(a.ax, ix, lnx, ox);

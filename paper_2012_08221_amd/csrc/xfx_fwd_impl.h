@@ -19,6 +19,7 @@
 // This is gather-plus-stencil work with no contraction: no MFMA.
 #pragma once
 
+#include "ln.h"
 #include "pdfx_internal.h"
 
 namespace pdfx {
@@ -234,8 +235,8 @@ __global__ __launch_bounds__(BLOCK) void xfx_kernel(const XfxArgs a)
                 qv = qv * qv;
             ok[j] = domain(a, xv, qv);
             count_flagged(live[j] && !ok[j], a.dom_count);
-            const double lnx = log(xv);
-            const double lnq = log(qv);
+            const double lnx = ln(xv);
+            const double lnq = ln(qv);
             const int ix = lbin(lx, xv, lnx);
             const int kq = lbin(lq, qv, lnq);
             weights<V>(lx, ix, lnx, wx[j]);

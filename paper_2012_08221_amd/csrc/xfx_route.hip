@@ -349,7 +349,7 @@ __global__ __launch_bounds__(kRouteBlock<V>) void xfx_route_kernel(const RouteAr
             fwd::count_flagged(live && !ok, a.dom_count);
             if constexpr (AS)
                 fwd::count_flagged(live && !q_ok, a.dom_count);
-            const double lnx = log(xv), lnq = log(qv);
+            const double lnx = ln(xv), lnq = ln(qv);
             V wx[4], wq[4];
             const int ix = piece_bin(px, xv, lnx);
             const int kq = piece_bin(pq, qv, lnq);
@@ -467,7 +467,7 @@ __global__ __launch_bounds__(kRouteBlock<V>) void xfx_route_kernel(const RouteAr
                 const int flags = (ok ? 0 : 1) + (AS && !q_ok ? 1 : 0);
                 if (flags)   // only some lanes are here
                     atomicAdd(a.dom_count, (unsigned long long)flags);
-                const double lnx = log(xv), lnq = log(qv);
+                const double lnx = ln(xv), lnq = ln(qv);
                 V wx[4], wq[4];
                 const int ix = far_weights<V>(md.ax, xv, lnx, wx);
                 const int kq = far_weights<V>(md.aq, qv, lnq, wq);
