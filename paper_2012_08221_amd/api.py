@@ -39,8 +39,15 @@ def _device_f64(a, device=None) -> torch.Tensor:
     return torch.as_tensor(np.asarray(a, dtype=np.float64), device=device or "cuda")
 
 
+# The current stream's handle without a Stream object around it (0.1 us instead of 2 of a
+# small call's 13); absent from builds of torch without a GPU.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(device=None) -> int:
-    return torch.cuda.current_stream(device).cuda_stream
+    if _raw_stream is None or device is None or device.type != "cuda" or device.index is None:
+        return torch.cuda.current_stream(device).cuda_stream
+    return _raw_stream(device.index)
 
 
 def _ptr(t):
@@ -118,6 +125,16 @@ class PDF:
 
     def _points(self, *arrays):
         """FP64 contiguous tensors on the grid's device, of one length."""
+        # the usual arguments are taken as they are (0.7 us instead of 1.8 of a small
+        # call's 13)
+        dev, n = self.device, None
+        for a in arrays:
+            if (type(a) is not torch.Tensor or a.dtype is not torch.float64 or a.device != dev
+                    or not a.is_contiguous() or (n is not None and a.numel() != n)):
+                break
+            n = a.numel()
+        else:
+            return list(arrays)
         ts = [_device_f64(a, self.device) for a in arrays]
         for t in ts:
             _on_device(t, self.device, "points")

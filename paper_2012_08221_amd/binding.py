@@ -184,8 +184,12 @@ def pdfx_free_grid(h: int):
 
 
 def _pids(pids):
-    arr = np.ascontiguousarray(np.atleast_1d(pids), dtype=np.int32)
-    return arr, arr.ctypes.data
+    if (type(pids) is np.ndarray and pids.ndim == 1 and pids.dtype == np.int32
+            and pids.flags.c_contiguous):
+        arr = pids
+    else:
+        arr = np.ascontiguousarray(np.atleast_1d(pids), dtype=np.int32)
+    return arr, arr.__array_interface__["data"][0]   # (arr.ctypes.data takes twice as long)
 
 
 def pdfx_eval_xfx(h, xf_dev, prec, pids, x_ptr, q2_ptr, n_pts, out_ptr, domain_mode, stream):
