@@ -244,6 +244,9 @@ bool dma_alphas_fit(int nx, int nq, bool f32);
 // the bordered group slabs); stages and slots planned as for the group kernels.
 bool xfx_direct_fits(const XfxArgs &a);
 hipError_t launch_xfx_direct(const XfxArgs &a, bool f32, bool raw, hipStream_t s);
+// The same with a group's nodes in LDS, for more points (a.n < 2^31 * 8).
+bool xfx_group_fits(const XfxArgs &a);
+hipError_t launch_xfx_group(const XfxArgs &a, bool f32, int cus, hipStream_t s);
 hipError_t launch_alphas(const AlphasArgs &a, bool f32, hipStream_t s);
 hipError_t launch_repack(const RepackArgs &a, bool f32, hipStream_t s);
 hipError_t launch_set(const SetArgs &a, bool f32, LaunchShape ls, size_t lds, int cus, hipStream_t s);

@@ -101,20 +101,34 @@ struct RouteArgs {
     void *as_out;
 };
 
-// Points from which a call is routed (below, placing the pieces takes longer
-// than they save).  Grids of the double-buffered forward kernel (100 x 50
-// knots, 11 partons, FP64 / FP32): 256 thousand points 32 / 23 us there and
-// 37 / 32 us routed, 512 thousand 57 / 38 and 52 / 40.  Larger grids (190 x 75):
-// 128 thousand 45 / 24 and 38 / 30, 256 thousand 81 / 43 and 47 / 36.
+// Which kernel takes a call.  Its load is its points times the request's flavour groups
+// (11 partons: 6 in FP64, 3 in FP32).
+//
+// Up to kDirectMost the direct kernel, whose gathers come from the L2, then the group
+// kernel, which copies a group's nodes into LDS first.  100 x 50 knots, FP64 / FP32 us,
+// 11 partons: 8 thousand points 6.2 / 5.1 and 5.5 / 5.2, 16 thousand 6.8 / 5.4 and 6.3 /
+// 5.7, 32 thousand 10.0 / 6.6 and 7.6 / 6.3, 100 thousand 27 / 15 and 13.3 / 8.9 (the
+// double-buffered kernel 18.8 / 13.3); 2 partons: 32 thousand 5.6 / 5.7 and 5.6 / 5.5.
+// Caller values are read by the direct kernel as they are and repacked for the group
+// kernel: the line is their points times partons (11: 16 thousand 7.8 / 6.4 and 9.6 / 8.2,
+// 32 thousand 11.8 / 8.7 and 10.7 / 8.7; 2: 100 thousand 7.4 / 7.9 and 10.5 / 8.5).
+constexpr int64_t kDirectMost = 60000, kDirectMostRaw = 250000;
+// From kRouteMin the routed kernel, whose placing of the pieces takes 20 us: 11 partons,
+// group and routed: 400 thousand points 41 / 22.5 and 46 / 36, 600 thousand 58 / 30 and
+// 55 / 43, 1 million 90 / 46 and 73 / 52, 2 million 167 / 87 and 115 / 77; 110 x 70 knots:
+// 600 thousand 55 / 31 and 58 / 44, 1 million 90 / 47 and 78 / 56; 5 partons: 600 thousand
+// 31 / 21 and 41 / 29, 2 million 87 / 55 and 74 / 52.
+constexpr int64_t kRouteMin = 3000000;
+// Calls that cannot be routed: 12 columns with a repeated pid, double-buffered and group,
+// 2 million points 206 / 127 and 199 / 120, 10 million 944 / 583 and 1222 / 575; 60 x 25
+// knots 2 million 169 / 109 and 183 / 116; 3 columns 10 million 488 / 297 and 282 / 153.
+constexpr int64_t kGroupMostDma = 6000000;
+// Grids whose group does not fit the group kernel, and requests of more flavours than it
+// takes: points from which they are routed, the direct kernel (if it takes them) before.
+// 190 x 75 knots: 100 thousand points 29.4 / 16.6 by the direct kernel and 47.6 / 29.1 by
+// the single-buffer one, 128 thousand 38 / 30 routed and 45 / 24, 256 thousand 47 / 36 and
+// 81 / 43.
 constexpr int64_t kRouteMinDma = 400000, kRouteMinOther = 200000;
-// Points times flavour groups up to which a call on a grid of the double-buffered
-// kernel goes to the direct kernel; calls on larger grids do so until they are
-// routed.  100 x 50 knots, 11 partons in 6 groups (FP64) / 3 (FP32), double-buffered
-// and direct: 32 thousand points 17.8 / 13.0 us and 9.6 / 7.4, 64 thousand 18.5 /
-// 13.3 and 20.6 / 10.2, 100 thousand 19.1 / 13.8 and 27.3 / 15.3; 2 partons in 2
-// groups: 100 thousand 12.2 / 10.2 and 10.5 / 8.0.  190 x 75: 100 thousand points
-// 47.6 / 29.1 us by the single-buffer kernel and 29.4 / 16.6.
-constexpr int64_t kDirectMaxDma = 250000;
 // The same for a set: points per member and points over all members.  101
 // members in FP64 / FP32 by the class kernels and routed: 32 thousand points
 // 359 / 238 us and 415 / 280, 64 thousand 724 / 450 and 558 / 368; 8 members:

@@ -1034,7 +1034,8 @@ static int run_route(const pdfx_grid *g, const XfxArgs &a, const void *xf_dev, i
     return PDFX_OK;
 }
 
-// Repack caller values (if any) and launch the forward kernel.  Shapes with
+// Repack caller values (if any) and launch the forward kernel: by size the direct, the
+// group or the routed kernel (route_internal.h), unless the launch shape is set.  Shapes with
 // results held in registers (ppt > 0) use the flavour-group kernels when the
 // request's groups fit them: the double-buffered one when the grid fits its
 // LDS and `out` is 16-byte aligned, else the single-buffer one when its slab
@@ -1047,8 +1048,15 @@ int run_xfx(const pdfx_grid *g, XfxArgs &a, const void *xf_dev, int prec, hipStr
     if (as_done)
         *as_done = false;
     LaunchShape ls = g->shape[prec];
-    if (!g->shape_pinned[prec] && a.n_u == a.n_req &&
-        a.n >= (g->dma_grid ? kRouteMinDma : kRouteMinOther)) {
+    const bool pinned = g->shape_pinned[prec];
+    const bool staged = ls.ppt > 0 && plan_stages(a, f32 ? 4 : 2);
+    const int64_t load = a.n * (staged ? std::max(a.n_stage, 1) : 1);
+    bool group = staged && !pinned && xfx_group_fits(a);
+    const bool direct = staged && !pinned && xfx_direct_fits(a) &&
+                        (!group ? a.n <= kRouteMinOther
+                                : xf_dev ? a.n * a.n_u <= kDirectMostRaw : load <= kDirectMost);
+    if (!pinned && !direct && a.n_u == a.n_req &&
+        (group ? load >= kRouteMin : a.n >= (g->dma_grid ? kRouteMinDma : kRouteMinOther))) {
         bool done = false;
         const int rc = run_route(g, a, xf_dev, prec, s, &done);
         if (rc != PDFX_OK || done) {
@@ -1057,26 +1065,34 @@ int run_xfx(const pdfx_grid *g, XfxArgs &a, const void *xf_dev, int prec, hipStr
             return rc;
         }
     }
-    if (!g->shape_pinned[prec] && ls.ppt > 1) {
-        // a small call: (512, 1) gives twice or more the workgroups
-        const int64_t tile = (int64_t)ls.block * ls.ppt;
-        if ((a.n + tile - 1) / tile < g->cus / 2)
-            ls = LaunchShape{512, 1};
-    }
-    const bool staged = ls.ppt > 0 && plan_stages(a, f32 ? 4 : 2);
-    const int64_t direct_most = g->dma_grid ? kDirectMaxDma / std::max(a.n_stage, 1) : kRouteMinOther;
-    if (staged && !g->shape_pinned[prec] && a.n <= direct_most && xfx_direct_fits(a)) {
-        if (xf_dev) {
+    // not routed (a repeated pid, ...): wide rows of many points, which the groups
+    // write in parts, go to the double-buffered kernel
+    if (group && g->dma_grid && a.n_stage > 2 && load >= kGroupMostDma && (uintptr_t)a.out % 16 == 0)
+        group = false;
+    if (direct || group) {
+        a.gvals = g->gvals[prec].ptr;
+        a.gstride = g->gstride;
+        if (xf_dev && direct) {
             a.vals = xf_dev;
-        } else {
-            a.gvals = g->gvals[prec].ptr;
-            a.gstride = g->gstride;
+        } else if (xf_dev) {
+            if ((e = launch_grp_repack(xf_dev, g->scratch_gvals[prec].ptr, g->nf, a.nx, a.nq,
+                                       g->n_groups[prec], g->gstride, true, f32, s)) != hipSuccess)
+                return fail_hip(e, "repack launch");
+            a.gvals = g->scratch_gvals[prec].ptr;
         }
-        if ((e = launch_xfx_direct(a, f32, xf_dev != nullptr, s)) != hipSuccess)
+        e = direct ? launch_xfx_direct(a, f32, xf_dev != nullptr, s)
+                   : launch_xfx_group(a, f32, g->cus, s);
+        if (e != hipSuccess)
             return fail_hip(e, "xfx launch");
         if (as_done)
             *as_done = a.as_out != nullptr;
         return PDFX_OK;
+    }
+    if (!pinned && ls.ppt > 1) {
+        // a small call: (512, 1) gives twice or more the workgroups
+        const int64_t tile = (int64_t)ls.block * ls.ppt;
+        if ((a.n + tile - 1) / tile < g->cus / 2)
+            ls = LaunchShape{512, 1};
     }
     if (staged && g->dma_grid && (uintptr_t)a.out % 16 == 0 &&
         dma_supported(ls, a.nx, a.nq, a.ax.nbuckets, a.aq.nbuckets, f32)) {

@@ -10,7 +10,7 @@ from paper_2012_08221_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
 
-N = 400_003   # past the point where every grid's calls are routed, no multiple of a tile
+N = 3_000_003   # past the point where every grid's calls are routed, no multiple of a tile
 
 
 @pytest.fixture(scope="module")
@@ -234,11 +234,11 @@ def test_integrand_fewer_quarks(api, torch, quarks, prec):
     dy_both(api, torch, g, u1, u2, prec)
 
 
-# ---- the direct kernel of small calls ----
+# ---- the direct kernel of small calls and the group kernel above it ----
 
 @pytest.mark.parametrize("prec", ["f64", "f32s"])
-@pytest.mark.parametrize("geo", [(100, 3, 50), (190, 4, 75), (9, 2, 8)])
-@pytest.mark.parametrize("n", [1, 63, 64, 65, 3001])
+@pytest.mark.parametrize("geo", [(100, 3, 50), (190, 4, 75), (9, 2, 8), (110, 2, 70)])
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 3001, 60_001, 300_007])
 def test_small_calls_same_bits(api, torch, geo, n, prec):
     nx, nsub, nq = geo
     g = wl.make_grid(wl.draw_params(np.random.default_rng(21)), nx, wl.MEMBER_EDGES[nsub], nq)
