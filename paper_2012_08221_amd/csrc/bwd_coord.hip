@@ -443,10 +443,10 @@ __global__ __launch_bounds__(kKnotBlock) void knot_grad_kernel(const BwdArgs a, 
         double wx[4], wq[4], wa[4], wb[4];
         fold_pair(tx, cx[ix], wx);
         fold_pair(tq, cq[kq], wq);
-        const int sx = fwd::window(ix, nx, wx), sq = fwd::window(kq, nq, wq);
+        const int sx = visit_start(ix, nx), sq = visit_start(kq, nq);
         int row[4], colw[4];
-        visit_weights(SWAPPED ? wq : wx, SWAPPED ? sq : sx, key, wa);
-        visit_weights(SWAPPED ? wx : wq, SWAPPED ? sx : sq, key >> 2, wb);
+        visit_weights(SWAPPED ? wq : wx, SWAPPED ? kq : ix, key, wa);
+        visit_weights(SWAPPED ? wx : wq, SWAPPED ? ix : kq, key >> 2, wb);
         visit_rows<8 * kKnotGroup>(SWAPPED ? sq : sx, y.strip, key, row);
         visit_cols<8 * kKnotGroup>(SWAPPED ? sx : sq, key, colw);
         LdsWord *word[4][4];

@@ -454,23 +454,22 @@ __global__ __launch_bounds__(kPairBlock) void dy_pair_adjoint_kernel(const DyArg
         fold_pair(st.t1, c1, w1);
         fold_pair(st.t2, c2, w2);
         fold_pair(st.tq, cc, wq);
-        const int sq = fwd::window(kq, nq, wq);
-        const int s1 = fwd::window(i1, nx, w1), s2 = fwd::window(i2, nx, w2);
+        const int sq = visit_start(kq, nq), s1 = visit_start(i1, nx), s2 = visit_start(i2, nx);
         // everything below in the lane's order: u[i] the weights along x, uq[k] along Q^2
         double u1[4], u2[4], uq[4];
         int l1[4], l2[4], lq1[4], lq2[4];
         if constexpr (SWAPPED) {
-            visit_weights(wq, sq, key, uq);
-            visit_weights(w1, s1, key >> 2, u1);
-            visit_weights(w2, s2, key >> 2, u2);
+            visit_weights(wq, kq, key, uq);
+            visit_weights(w1, i1, key >> 2, u1);
+            visit_weights(w2, i2, key >> 2, u2);
             visit_rows<8>(sq, y.strip, key, lq1);
             visit_rows<8>(sq, -y.strip, key, lq2);
             visit_cols<8>(s1, key, l1);
             visit_cols<8>(s2, key, l2);
         } else {
-            visit_weights(wq, sq, key >> 2, uq);
-            visit_weights(w1, s1, key, u1);
-            visit_weights(w2, s2, key, u2);
+            visit_weights(wq, kq, key >> 2, uq);
+            visit_weights(w1, i1, key, u1);
+            visit_weights(w2, i2, key, u2);
             visit_rows<8>(s1, y.strip, key, l1);
             visit_rows<8>(s2, -y.strip, key, l2);
             visit_cols<8>(sq, key, lq1);

@@ -56,10 +56,20 @@ __device__ __forceinline__ double pick(double a, double b, unsigned long long ma
     return __longlong_as_double((long long)((unsigned long long)hi << 32 | lo));
 }
 
-// o[s] = w[((s ^ l) - r) mod 4]: the weights of a window starting at r in the order
-// in which a lane with key l visits its positions.
-__device__ __forceinline__ void visit_weights(const double w[4], int r, int l, double o[4])
+// First knot of the window of interval i on an axis of n >= 4 knots.
+__device__ __forceinline__ int visit_start(int i, int n)
 {
+    return min(max(i - 1, 0), n - 4);
+}
+
+// The weights w of knots i-1 .. i+2 in the order in which a lane with key l visits the
+// positions of interval i's window: o[s] is the weight of the knot at position s ^ l,
+// w[((s ^ l) - (i - 1)) mod 4].  At either end of the axis the window starts a knot
+// later or earlier; the knot it has instead is congruent to the one outside, whose
+// weight is 0.
+__device__ __forceinline__ void visit_weights(const double w[4], int i, int l, double o[4])
+{
+    const int r = i - 1;
     const unsigned long long odd = __ballot(r & 1), flip = __ballot(l & 1),
                              half = __ballot(((r >> 1) ^ (l >> 1)) & 1);
     double t[4], u[4];
