@@ -289,8 +289,8 @@ __global__ __launch_bounds__(BLOCK) void coord_grad_kernel(const CoordArgs c)
 // (scatter_order.h), so that the lanes of an add hit different banks; the next
 // step's state is loaded a step ahead.  The two constants of each interval that the
 // weights need are in LDS (the records in global memory, eight gathers a point,
-// kept the pass waiting).  1e6 points x 11 FP32 flavours on 100 x 50 knots: 76 us, 41
-// of them vector instructions and 27 LDS adds (the adds in one order, lanes dealt over
+// kept the pass waiting).  1e6 points x 11 FP32 flavours on 100 x 50 knots: 74 us, 38
+// of them vector instructions, 27 LDS adds and 11 the sums' way out (the adds in one order, lanes dealt over
 // the banks by their windows instead: 83 us).  The sums are kept in 64-bit fixed point
 // (fixed_point.h), with the scale of each flavour taken from the max of
 // finite |dL/dout| (left per workgroup by the coordinate pass, else found by
@@ -384,23 +384,7 @@ __global__ __launch_bounds__(kKnotBlock) void knot_grad_kernel(const BwdArgs a, 
         m[kKnotGroup] = fmax(m[kKnotGroup], weight_sum_bound(a.ax.rec64[i]));
     for (int i = threadIdx.x; i < nq - 1; i += kKnotBlock)
         m[kKnotGroup + 1] = fmax(m[kKnotGroup + 1], weight_sum_bound(a.aq.rec64[i]));
-#pragma unroll
-    for (int j = 0; j < kKnotGroup + 2; ++j) {
-        double v = m[j];
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1)
-            v = nan_max(v, __shfl_xor(v, d));
-        if ((threadIdx.x & 63) == 0)
-            wmax[j][threadIdx.x >> 6] = v;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < kKnotGroup + 2; ++j) {
-        double v = wmax[j][0];
-        for (int w = 1; w < kKnotBlock / 64; ++w)
-            v = nan_max(v, wmax[j][w]);
-        m[j] = v;
-    }
+    block_max<kKnotGroup + 2, kKnotBlock / 64>(m, &wmax[0][0]);
     // the scales are the same in every lane: held in scalar registers
     auto uniform = [](double v) {
         const long long b = __double_as_longlong(v);

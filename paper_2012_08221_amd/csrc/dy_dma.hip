@@ -320,9 +320,10 @@ hipError_t dy_dma_typed(const DyArgs &a, LaunchShape ls, int cus, hipStream_t s,
 // its lane in the last bit); the constants that the weights need are in LDS.  The sums
 // are kept in 64-bit fixed point (integer LDS adds run ~1.9x faster than FP64 ones, and
 // integer sums are exact and independent of the order of the adds).  1e7 points, 100 x
-// 50 knots, FP64: 870 us, 620 of them vector instructions and 433 LDS; in one order, with
+// 50 knots, FP64: 857 us, 590 of them vector instructions and 433 LDS; in one order, with
 // the points dealt to lanes by the bank of the quark's stencil and the interval records
-// gathered from global memory, 1076 us (926 of them LDS).  The scale is a power of two per workgroup and array,
+// gathered from global memory, 1076 us (926 of them LDS).  1e5 points 28 us (31).
+// The scale is a power of two per workgroup and array,
 // from a bound on the terms: |alpha_s| <= B_a max|alpha knot|, a partner value
 // <= B_x B_q max|row value|, one weight product <= B_x B_q, with B the largest
 // sum of |weights| over an axis' intervals (1 + 4/27 times the sum of the
@@ -365,14 +366,24 @@ __global__ __launch_bounds__(kPairBlock) void dy_pair_adjoint_kernel(const DyArg
     // m[0..5]: max |quark value|, max |antiquark value|, weight-sum bounds of
     // the x, Q^2 and alpha_s axes, max |alpha_s knot value|
     double m[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int e = threadIdx.x; e < nodes; e += kPairBlock) {
-        const V u = src[((size_t)(rq / G) * a.gstride + e) * G + rq % G];
-        const V ub = src[((size_t)(rqb / G) * a.gstride + e) * G + rqb % G];
-        const int i = e / nq, k = e - i * nq;
-        vals[pair_word(y, false, i, k)] = (double)u;
-        vals[pair_word(y, true, i, k)] = (double)ub;
-        m[0] = nan_max(m[0], fabs((double)u));
-        m[1] = nan_max(m[1], fabs((double)ub));
+    // (five at once: a grid of up to 5000 knots loads all its values before it waits)
+    for (int e0 = threadIdx.x; e0 < nodes; e0 += 5 * kPairBlock) {
+        V u[5], ub[5];
+#pragma unroll
+        for (int t = 0; t < 5; ++t) {
+            const int e = min(e0 + t * kPairBlock, nodes - 1);
+            u[t] = src[((size_t)(rq / G) * a.gstride + e) * G + rq % G];
+            ub[t] = src[((size_t)(rqb / G) * a.gstride + e) * G + rqb % G];
+        }
+#pragma unroll
+        for (int t = 0; t < 5; ++t) {
+            const int e = min(e0 + t * kPairBlock, nodes - 1);
+            const int i = e / nq, k = e - i * nq;
+            vals[pair_word(y, false, i, k)] = (double)u[t];
+            vals[pair_word(y, true, i, k)] = (double)ub[t];
+            m[0] = nan_max(m[0], fabs((double)u[t]));
+            m[1] = nan_max(m[1], fabs((double)ub[t]));
+        }
     }
     for (int i = threadIdx.x; i < nx - 1; i += kPairBlock) {
         const IntervalRec<double> r = a.ax.rec64[i];
@@ -390,25 +401,7 @@ __global__ __launch_bounds__(kPairBlock) void dy_pair_adjoint_kernel(const DyArg
         m[4] = fmax(m[4], weight_sum_bound(a.aa.rec64[i]));
     for (int i = threadIdx.x; i < a.aa.n + 2; i += kPairBlock)
         m[5] = fmax(m[5], fabs(a.as_vals64[i]));
-    // the waves' maxima meet in the gradients' place
-    double *const wmax = reinterpret_cast<double *>(gq);
-#pragma unroll
-    for (int j = 0; j < 6; ++j) {
-        double v = m[j];
-#pragma unroll
-        for (int k = 1; k < 64; k <<= 1)
-            v = nan_max(v, __shfl_xor(v, k));
-        if ((threadIdx.x & 63) == 0)
-            wmax[j * (kPairBlock / 64) + (threadIdx.x >> 6)] = v;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < 6; ++j) {
-        double v = wmax[j * (kPairBlock / 64)];
-        for (int w = 1; w < kPairBlock / 64; ++w)
-            v = nan_max(v, wmax[j * (kPairBlock / 64) + w]);
-        m[j] = v;
-    }
+    block_max<6, kPairBlock / 64>(m, reinterpret_cast<double *>(gq));   // in the gradients' place
     __syncthreads();
     for (int e = threadIdx.x; e < y.words; e += kPairBlock)
         gq[e] = 0ull;

@@ -31,6 +31,34 @@ __device__ __forceinline__ unsigned long long to_fixed(double c, double f)
     return (unsigned long long)((unsigned)(t >> 32) - 0x43380000u) << 32 | (unsigned)t;
 }
 
+// Max over the workgroup's WAVES waves of each m[j] (NaN wins), in every thread; red:
+// N * WAVES doubles of LDS.
+template <int N, int WAVES>
+__device__ __forceinline__ void block_max(double (&m)[N], double *red)
+{
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        double v = m[j];
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1)
+            v = nan_max(v, __shfl_xor(v, d));
+        if ((threadIdx.x & 63) == 0)
+            red[j * WAVES + (threadIdx.x >> 6)] = v;
+    }
+    __syncthreads();
+    // one thread a value: reading N * WAVES of them in each spilled 72 registers (13 us)
+    if (threadIdx.x < N) {
+        double v = red[threadIdx.x * WAVES];
+        for (int w = 1; w < WAVES; ++w)
+            v = nan_max(v, red[threadIdx.x * WAVES + w]);
+        red[threadIdx.x * WAVES] = v;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < N; ++j)
+        m[j] = red[j * WAVES];
+}
+
 // Fixed-point exponent for terms bounded by bnd, summed at most n at a time.
 // Kept within [-1000, 1000], so that 2^S and 2^-S are normal doubles; bounds
 // below ~2^-950 then give terms that round to 0.
