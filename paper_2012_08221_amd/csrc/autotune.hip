@@ -269,6 +269,7 @@ extern "C" int pdfx_autotune_set(pdfx_set *s, int prec, int32_t n_req, int64_t n
         cand.push_back(set_shape_at(i));
     if (prec == PDFX_F32S)
         cand.push_back(LaunchShape{512, 4});
+    s->tuning = true;   // the shapes are those of the calls that are not routed
     for (const LaunchShape ls : cand) {
         for (int tpi : {1, 2, 4, 8}) {
             s->shape[prec] = ls;
@@ -287,6 +288,7 @@ extern "C" int pdfx_autotune_set(pdfx_set *s, int prec, int32_t n_req, int64_t n
             }
         }
     }
+    s->tuning = false;
     s->shape[prec] = best_ls;
     s->tiles_per_item[prec] = best_tpi;
     hipError_t e = hipDeviceSynchronize();

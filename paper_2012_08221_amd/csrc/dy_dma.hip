@@ -316,7 +316,7 @@ hipError_t dy_dma_typed(const DyArgs &a, LaunchShape ls, int cus, hipStream_t s,
 // a 16-tap stencil of the other flavour's slab.  The LDS gradients are added
 // to the FP64 accumulator at the end.  The 32 adds of a point are made in its lane's
 // own order over a blocked layout (scatter_order.h), so that the lanes of an add hit
-// different banks, and so are its 32 reads (the stencil sums of a point then depend on
+// different banks, and so are its 32 reads (its stencil sums of a point then depend on
 // its lane in the last bit); the constants that the weights need are in LDS.  The sums
 // are kept in 64-bit fixed point (integer LDS adds run ~1.9x faster than FP64 ones, and
 // integer sums are exact and independent of the order of the adds).  1e7 points, 100 x
@@ -332,6 +332,7 @@ hipError_t dy_dma_typed(const DyArgs &a, LaunchShape ls, int cus, hipStream_t s,
 // Non-finite inputs make the two rows' gradients NaN.
 
 constexpr int kPairBlock = 1024;
+
 // Where the pair's knots lie: the quark's in strips of 4 lines upwards from word 0, the
 // antiquark's in strips downwards from `down`.  If the last strip holds 1 or 2 lines,
 // the two flavours' share its words, so that 100 x 50 FP64 knots fit with strips of a

@@ -11,7 +11,7 @@
 // points are as in the routed x f kernel; bins, weights and the order of sums are
 // those of the other integrand kernels, so each point's value is the same bits.
 // Bound by the LDS gathers (160 values a point in FP64: 1280 bytes).  10 million
-// points, 100 x 50 knots: 973 -> 480 us FP64, 726 -> 292 us FP32 against the
+// points, 100 x 50 knots: 973 -> 438 us FP64, 726 -> 273 us FP32 against the
 // double-buffered kernel's default shape.
 #include "dy_route.h"
 #include "piece_axis.h"

@@ -1699,7 +1699,8 @@ int pdfx_eval_set_xfx(const pdfx_set *s, int prec, const int32_t *pids, int32_t 
     };
     RouteArgs r{};
     route_teams(s->cus, &r);
-    bool route = fa.n_u == n_req && n_pts >= (dma ? kRouteMinSet : kRouteMinSetOdd) &&
+    bool route = !s->tuning && fa.n_u == n_req &&
+                 n_pts >= (dma ? kRouteMinSet : kRouteMinSetOdd) &&
                  n_pts * a.n_mem >= (dma ? kRouteMinSetAll : kRouteMinSetOddAll);
     for (int m = 0; m < a.n_mem && route; ++m) {
         const pdfx_grid *g = s->members[m];

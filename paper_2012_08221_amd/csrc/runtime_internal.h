@@ -141,6 +141,7 @@ struct pdfx_set {
     mutable int64_t host_count = 0;
     pdfx::LaunchShape shape[2] = {{512, 2}, {512, 2}};
     int tiles_per_item[2] = {4, 4};
+    bool tuning = false;                     // launch shapes are being timed: nothing is routed
     int cus = 256;
     // double-buffered classes (set_dma.hip): members by node width, per precision
     pdfx::DeviceBuf dma_mem;                 // SetMemberDev[n_mem]

@@ -1,5 +1,5 @@
-// Direct forward kernel for small calls: batched x f(x, Q^2) without the grid in
-// LDS.
+// Forward kernels for calls below the routed kernel's: the direct kernel (small calls,
+// without the grid in LDS) and the group kernel (medium ones, a flavour group in LDS).
 //
 // A call of a few thousand points is latency: the kernels that bring the grid into
 // LDS copy 160 KB per workgroup and walk the flavour groups one after another.

@@ -25,10 +25,10 @@
 // two thirds of that in bank conflicts of the random 16-byte gathers) and by the
 // vector ALU and the LDS alike in FP32; rows that are finished by two
 // workgroups cost up to 60% more HBM writes than the rows' bytes.  10 million
-// points, 11 partons and alpha_s on 100 x 50 knots: 934 -> 497 us FP64 and 588 ->
-// 308 us FP32 against the double-buffered kernel's default shape; 3 million
-// points, 5 partons on 150 x 60 knots, continued outside: 345 -> 130 us; 101
-// members of 200003 points FP64: 4.37 -> 1.16 ms, of 1 million FP32: 5.97 -> 3.13.
+// points, 11 partons and alpha_s on 100 x 50 knots: 934 -> 489 us FP64 and 588 ->
+// 302 us FP32 against the double-buffered kernel's default shape; 3 million
+// points, 5 partons on 150 x 60 knots, continued outside: 345 -> 125 us; 101
+// members of 200003 points FP64: 4.37 -> 1.13 ms, of 1 million FP32: 5.97 -> 2.95.
 #include "piece_axis.h"
 #include "set_internal.h"
 
