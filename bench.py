@@ -76,40 +76,37 @@ def forward_kernel_sources():
     """Sources of the forward kernels (any change voids recorded counters)."""
     import glob
     csrc = os.path.join(HERE, "paper_2012_08221_amd", "csrc")
-    return sorted(glob.glob(os.path.join(csrc, "xfx_*"))) + [os.path.join(csrc, "pdfx_internal.h")]
+    return sorted(glob.glob(os.path.join(csrc, "xfx_*"))) + [
+        os.path.join(csrc, f) for f in ("ln.h", "pdfx_internal.h", "piece_axis.h", "route_internal.h")]
 
 
-def forward_kernel_name(prec, launch):
-    """Kernel that pdfx_eval_xfx_alphas runs for the bench grid (it fits the
-    double-buffered kernel, and its alpha_s knots are its Q^2 knots, so x f and
-    alpha_s come from one pass) with launch shape (block, ppt)."""
+def forward_kernel_name(prec, n, nf):
+    """Kernel that pdfx_eval_xfx_alphas runs for n points of the bench grid with no launch
+    shape set: by points times flavour groups the direct, the group or the routed kernel
+    (its alpha_s knots are its Q^2 knots, so x f and alpha_s come from one pass)."""
     v = "double" if prec == "f64" else "float"
-    block, ppt = launch
-    if ppt > 0:
-        return "xfx_dma_kernel<%s, %d, %d, true>" % (v, block, ppt)
-    return "xfx_kernel<%s, %d, %d, PF, DB, 0>" % (v, block, -ppt)
+    g = 2 if prec == "f64" else 4
+    load = n * ((nf + g - 1) // g)
+    if load >= 3_000_000:
+        return "xfx_route_kernel<%s, true>" % v
+    return "xfx_group_kernel<%s, true>" % v if load > 60_000 else "xfx_direct_kernel<%s, true, false>" % v
 
 
-def lds_bytes(prec, launch, n, nf, nx, nq):
-    """LDS bytes one forward launch moves (double-buffered kernel, ppt > 0):
-    stencil reads (16 nodes of 16 B per point and flavour group), global-to-
-    LDS slab copies (one slab per group and tile), the output rows staged
-    through LDS (written, then read) and the four alpha_s values per point.
-    None for the per-flavour kernel."""
-    block, ppt = launch
-    if ppt <= 0:
-        return None
+def lds_bytes(prec, n, nf):
+    """LDS bytes of the stencil reads of one routed forward launch: 16 nodes a point of
+    every full 16-byte plane and of the rest (8 bytes for 1 FP64 flavour, 4, 8 or 16 for 1,
+    2 or 3 FP32 ones), and the four alpha_s values."""
     vb = 8 if prec == "f64" else 4
     g = 16 // vb
-    stages = (nf + g - 1) // g
-    tiles = (n + block * ppt - 1) // (block * ppt)
-    return n * stages * 16 * 16 + tiles * stages * nx * nq * 16 + 2 * n * nf * vb + n * 4 * vb
+    left = nf % g
+    tail = 0 if left == 0 else vb * (4 if left == 3 else left)
+    return n * (16 * (nf // g * 16 + tail) + 4 * vb)
 
 
-def recorded_traffic(prec, launch):
+def recorded_traffic(prec, n):
     """HBM bytes per launch of the forward kernel from the committed rocprofv3
     FETCH_SIZE / WRITE_SIZE record, if it was taken on the same kernel source,
-    precision and launch shape; otherwise None."""
+    precision and number of points; otherwise None."""
     import hashlib
     path = os.path.join(HERE, "profiles", "xfx_fwd_1e7x11_hbm_traffic.json")
     try:
@@ -121,7 +118,7 @@ def recorded_traffic(prec, launch):
         with open(f, "rb") as fh:
             h.update(fh.read())
     if (rec.get("kernel_source_sha256") != h.hexdigest() or rec.get("prec") != prec
-            or list(rec.get("launch_shape", [])) != list(launch)):
+            or rec.get("n_points") != n):
         return None
     return float(rec["traffic_bytes"])
 
@@ -219,24 +216,18 @@ def main():
             lds_cache.update(lds_read_gbs())
         return lds_cache
 
-    def dy_fractions(prec, npts, chunk, ms_f, ms_b, lds, atomics, nx, nq, shape):
+    def dy_fractions(prec, npts, ms_f, ms_b, lds, atomics):
         """LDS and VALU fractions of the integrand (bound by neither HBM nor
         MFMA).  Forward LDS: the method's 164 values per point (10 partons x 16
-        knots + 4 alpha_s) and the kernel's own node reads and slab copies, both
-        against the measured LDS read rates.  VALU: the stencil arithmetic (2
+        knots + 4 alpha_s), which are what the kernel reads, against the measured
+        LDS read rates.  VALU: the stencil arithmetic (2
         flops per multiply-add: 16 + 4 per parton, 4 for alpha_s) in the value
         precision plus the per-point FP64 work (3 weight folds of ~30 flops, 2 exp
         and 1 log at ~40 flops each, luminosity and Jacobian ~12), against
         MI355X's vector peaks.  Backward: 10 partons x 16 knot adds per point
         against the measured 64-bit LDS atomic rate."""
         vb = 8 if prec == "f64" else 4
-        g = 16 // vb
-        stencils = 6 if prec == "f64" else 4          # FP32: the middle group at both sides
-        slabs = 12 // g
-        tile = shape[0] * shape[1]
-        tiles = npts // chunk * ((chunk + tile - 1) // tile)
-        alg = npts * 164 * vb
-        kern = npts * stencils * 16 * 16 + tiles * slabs * nx * nq * 16
+        alg = kern = npts * 164 * vb
         t = ms_f * 1e-3
         f_val = 10 * 2 * 20 + 2 * 4                  # flops in the value precision
         f_64 = 3 * 30 + 3 * 40 + 12                    # FP64 flops per point
@@ -472,31 +463,16 @@ def main():
                                             1.0 / (nchunk * csize), gxf.data_ptr(),
                                             stream.cuda_stream)
 
-            # launch shape of the integrand kernel: the fastest on the first chunk
-            def fwd_one():
-                u1, u2 = us[0]
-                B.pdfx_eval_dy(pdf.handle, None, api.prec_code(prec), u1.data_ptr(),
-                               u2.data_ptr(), csize, wl.DY_XMIN, wl.SQRT_S_DY ** 2,
-                               outd.data_ptr(), sums.data_ptr(), stream.cuda_stream)
-            tune = {}
-            for shape in ((512, 1), (512, 2), (256, 2)) + (((512, 4),) if prec == "f32s" else ()):
-                pdf.set_dy_launch(prec, *shape)
-                tune[shape] = timed(fwd_one, 3)
-            best = min(tune, key=tune.get)
-            pdf.set_dy_launch(prec, *best)
             ms_f = timed(fwd_all, 2)
             ms_b = timed(bwd_all, 2)
             npts = nchunk * csize
-            fr = dy_fractions(prec, npts, csize, ms_f, ms_b, lds_meas_all(), atomics_all(),
-                              grid.n_x, grid.n_q, best)
+            fr = dy_fractions(prec, npts, ms_f, ms_b, lds_meas_all(), atomics_all())
             dres[prec] = {**fr, "forward_points_per_s": npts / (ms_f * 1e-3),
                           "backward_points_per_s": npts / (ms_b * 1e-3),
                           "forward_ms_per_chunk": ms_f / nchunk,
-                          "backward_ms_per_chunk": ms_b / nchunk,
-                          "forward_launch_shape": list(best),
-                          "forward_shape_ms_chunk0": {"%dx%d" % k: v for k, v in tune.items()}}
-            log("dy %s: forward %.3f ms/chunk (shape %s), backward %.3f ms/chunk" %
-                (prec, ms_f / nchunk, best, ms_b / nchunk))
+                          "backward_ms_per_chunk": ms_b / nchunk}
+            log("dy %s: forward %.3f ms/chunk, backward %.3f ms/chunk" %
+                (prec, ms_f / nchunk, ms_b / nchunk))
         variants["drell_yan"] = {"n_points": nchunk * csize, "chunk": csize, **dres}
         if args.only == "dy":
             print(json.dumps({"only": "dy", **variants["drell_yan"]}))
@@ -528,12 +504,6 @@ def main():
                 B.pdfx_eval_lumi(pdf.handle, None, code, pa, pb, None, x1.data_ptr(),
                                  x2.data_ptr(), None, 172.5 ** 2, nl, L.data_ptr(), S.data_ptr(),
                                  0, stream.cuda_stream)
-            tune = {}
-            for shape in ((512, 1), (512, 2), (256, 2)) + (((512, 4),) if prec == "f32s" else ()):
-                pdf.set_lumi_launch(prec, *shape)
-                tune[shape] = timed(run_sum, 3)
-            best = min(tune, key=tune.get)
-            pdf.set_lumi_launch(prec, *best)
             ms_s = timed(run_sum, 5)
             ms_b = timed(run_both, 5)
             vb = 8 if prec == "f64" else 4
@@ -542,9 +512,7 @@ def main():
                           "sum_hbm_frac": nl * (16 + vb) / ms_s / 1e6 / HBM_PEAK_GBS,
                           "pairs_and_sum_ms": ms_b,
                           "pairs_and_sum_hbm_gbs_algorithmic": nl * (16 + 5 * vb) / ms_b / 1e6,
-                          "pairs_and_sum_hbm_frac": nl * (16 + 5 * vb) / ms_b / 1e6 / HBM_PEAK_GBS,
-                          "launch_shape": list(best),
-                          "shape_sum_ms": {"%dx%d" % k: v for k, v in tune.items()}}
+                          "pairs_and_sum_hbm_frac": nl * (16 + 5 * vb) / ms_b / 1e6 / HBM_PEAK_GBS}
             log("lumi %s: sum %.3f ms, pairs+sum %.3f ms" % (prec, ms_s, ms_b))
             del S, L
         variants["lumi"] = {"n_points": nl, "pairs": [list(t) for t in zip(pa, pb)],
@@ -623,8 +591,8 @@ def main():
             "xfx_hbm_gbs_algorithmic": n * bpp / (r["xfx_ms"] * 1e-3) / 1e9,
             "hbm_roofline_pf_s": HBM_PEAK_GBS * 1e9 / bpp * nf,
             **err.get(prec, {})}
-        lb = lds_bytes(prec, r["launch"], n, nf, grid.n_x, grid.n_q)
-        if lb is not None:
+        if "route" in forward_kernel_name(prec, n, nf):
+            lb = lds_bytes(prec, n, nf)
             # LDS ceiling: the rates the device is measured to reach in this
             # run (pdfx_bench_lds), lane-consecutive reads as the peak
             ach = lb / (r["xfx_ms"] * 1e-3) / 1e9
@@ -655,8 +623,8 @@ def main():
                    "q_subgrids": [int(v) for v in np.diff(grid.q_off)], "prec": args.prec},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS,
-                     "traffic": recorded_traffic(args.prec, head["launch"]),
-                     "kernel": forward_kernel_name(args.prec, head["launch"]),
+                     "traffic": recorded_traffic(args.prec, n),
+                     "kernel": forward_kernel_name(args.prec, n, nf),
                      "bytes_per_point": bytes_per_pt,
                      "copy_gbs": copy, "frac_of_copy": achieved / copy,
                      "lds": variants.get(args.prec, {}).get("lds")},

@@ -290,10 +290,12 @@ int pdfx_autotune(pdfx_grid *g, int prec, int32_t n_req, int64_t n_pts, const ch
 int pdfx_autotune_set(pdfx_set *s, int prec, int32_t n_req, int64_t n_pts, const char *cache_path);
 
 /* Current launch shape of a grid: workgroup size and points per thread.
- * Large calls (from 400 thousand points on grids of up to 5000 knots, 200
- * thousand on others) whose pids are distinct and held by the grid do not use
- * it: they go to the routed kernel, which keeps the grid in LDS in pieces and has
- * one shape, unless pdfx_set_launch has set a shape.
+ * It is used only by what the size rule leaves: unless pdfx_set_launch has set a shape, a
+ * call goes by its points times its flavour groups (2 partons in FP64, 4 in FP32) to the
+ * direct kernel (up to 60 thousand), the group kernel, or from 3 million on, if its pids
+ * are distinct and held by the grid, the routed kernel, which keeps the grid in LDS in
+ * pieces.  Grids of more than some 8000 knots have no group kernel: the direct kernel takes
+ * up to 200 thousand points there, the routed one the larger calls.
  * A default or tuned shape with ppt > 1 gives way to (512, 1) in a forward
  * call whose points fill fewer workgroups than half the compute units (e.g.
  * 1e5 points): smaller tiles keep more compute units busy.  A shape set by
