@@ -75,11 +75,16 @@ __global__ __launch_bounds__(kLineBlock) void lumi_line_kernel(const LumiLineArg
         const int r = e / (nx - 1), i = e - r * (nx - 1);
         const double *v = line + r * nx;
         const IntervalRec<double> c = a.ax.rec64[i];
-        const double v1 = v[i], v2 = v[i + 1], d = v2 - v1;
-        // slopes at both ends, times the width (c.pl or c.pr is 0 at an end)
-        const double s1 = fma(c.pl, v1 - v[i > 0 ? i - 1 : 0], c.ql * d);
-        const double s2 = fma(c.pr, v[i + 2 < nx ? i + 2 : i + 1] - v2, c.qr * d);
+        const double v0 = c.pl != 0.0 ? v[i - 1] : v[i], v1 = v[i], v2 = v[i + 1];
+        const double v3 = c.pr != 0.0 ? v[i + 2] : v2, d = v2 - v1;
+        // slopes at both ends, times the width
+        const double s1 = fma(c.pl, v1 - v0, c.ql * d), s2 = fma(c.pr, v3 - v2, c.qr * d);
         cubic[e] = Cubic{(V)v1, (V)s1, (V)(3.0 * d - 2.0 * s1 - s2), (V)(s1 + s2 - 2.0 * d)};
+        // infinite values (a caller's): the weights are below 0 at the outer two knots, so
+        // this is what the sum of the products is inside the interval
+        if (!(fabs(s1) + fabs(s2) < 1.0 / 0.0))
+            cubic[e] = Cubic{(V)(v1 + v2 - (c.pl != 0.0 ? v0 : 0.0) - (c.pr != 0.0 ? v3 : 0.0)), V(0),
+                             V(0), V(0)};
     }
     __syncthreads();
 

@@ -252,3 +252,33 @@ def test_one_scale_by_lines_and_by_groups(grid, torch, n_pair, prec):
                         ok = ~np.isnan(s)
                         assert np.all(np.abs(s - t)[ok] <= tol[ok])
                     assert pdf.domain_errors() == grp.domain_errors()
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32s"])
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+@pytest.mark.parametrize("knot", [0, 1, 50, 98, 99])
+def test_one_scale_by_lines_with_a_knot_that_is_not_finite(grid, torch, knot, value, prec):
+    """A caller's infinite or NaN knot: the two kernels agree which points are infinite,
+    with which sign, and which are NaN."""
+    from paper_2012_08221_amd import api
+    rng = np.random.default_rng(knot)
+    pdf, grp = api.PDF(grid), api.PDF(grid)
+    grp.set_lumi_launch(prec, 512, 1)
+    xf = np.abs(grid.xf) + 0.5
+    k = int(np.searchsorted(grid.q2, MT2)) - 1
+    xf[list(grid.pids).index(5), knot, k:k + 2] = value   # below and above the scale
+    vals = torch.as_tensor(xf, dtype=api.prec_dtype(prec), device="cuda")
+    # (inside the intervals: at a knot the weights of its neighbours are 0)
+    i = rng.integers(0, len(grid.x) - 1, 5000)
+    f = rng.uniform(0.05, 0.95, 5000)
+    x1 = np.exp(np.log(grid.x[i]) * (1 - f) + np.log(grid.x[i + 1]) * f)
+    x2 = np.exp(rng.uniform(np.log(1e-4), -0.01, 5000))
+    kw = dict(q2_fixed=MT2, prec=prec, values=vals)
+    got, want = (p.lumi([5, 2], [2, 5], x1, x2, **kw)[0].cpu().numpy() for p in (pdf, grp))
+    # the group kernel's window at an axis end holds one knot more, at weight 0: NaN there
+    # for a knot that this kernel does not read
+    same = (np.isnan(got) == np.isnan(want)) & (np.isinf(got) == np.isinf(want))
+    same &= ~np.isinf(got) | (np.sign(got) == np.sign(want))
+    ends = (i <= 1) | (i >= len(grid.x) - 3)
+    assert np.all(same[~ends, 0])
+    assert np.isfinite(got).any() and not np.isfinite(got).all()
