@@ -34,8 +34,8 @@ struct CoordArgs {
 // Most workgroups of a pass that writes per-workgroup maxima (gmax).
 constexpr int kMaxPart = 1024;
 
-// Workgroups of launch_coord_grad for n points.
-int coord_grad_blocks(int64_t n, int cus);
+// Workgroups of launch_coord_grad.
+int coord_grad_blocks(const XfxArgs &a, bool f32, int cus);
 hipError_t launch_coord_grad(const CoordArgs &c, bool f32, int cus, hipStream_t s);
 
 // Knot gradient by groups of flavours per workgroup (grids of up to 5000

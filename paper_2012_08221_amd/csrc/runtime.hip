@@ -1304,7 +1304,7 @@ int eval_xfx_backward(const pdfx_grid *g, const void *xf_dev, int prec, const in
             ca.gacc = a.gacc;
             ca.n_gacc = (int64_t)nv;
             ca.gmax = a.gmax;
-            a.n_part = coord_grad_blocks(n, g->cus);
+            a.n_part = coord_grad_blocks(ca.x, prec == PDFX_F32S, g->cus);
         }
         if ((e = launch_coord_grad(ca, prec == PDFX_F32S, g->cus, s)) != hipSuccess)
             return fail_hip(e, "adjoint launch");

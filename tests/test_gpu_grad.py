@@ -536,3 +536,29 @@ def test_knot_gradient_is_the_adjoint(torch, mods, nx, nq):
         want = (gout * oracle.xfx(gp, pids, x, q)).sum(axis=0)
         got = (gv * vals).sum(axis=(1, 2))
         assert np.all(np.abs(got - want) <= n * 1e-15 * 20 * np.abs(vals).max()), (got, want)
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32s"])
+def test_coordinate_gradient_of_a_large_call_in_parts(torch, mods, prec):
+    """Past 3 x 1024 points a compute unit FP32 runs in larger workgroups: the same bits as
+    the same points in calls below that."""
+    api, ag = mods
+    pdf = api.mkPDF(cfg0_grid())
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    n = 3 * 1024 * cus + 1025
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    x = torch.exp(torch.rand(n, generator=gen, dtype=torch.float64, device="cuda") * -20.0)
+    q2 = torch.exp(torch.rand(n, generator=gen, dtype=torch.float64, device="cuda") * 16.0 + 1.5)
+    w = torch.randn(n, 3, generator=gen, dtype=api.prec_dtype(prec), device="cuda")
+    vals = torch.as_tensor(cfg0_grid().xf, dtype=api.prec_dtype(prec), device="cuda")
+
+    def grads(sl):
+        xs, qs = x[sl].clone().requires_grad_(), q2[sl].clone().requires_grad_()
+        out = ag.xfx(pdf, vals.requires_grad_(), [21, 2, -3], xs, qs, prec=prec)
+        return torch.autograd.grad(out, (xs, qs), w[sl])
+
+    whole = grads(slice(None))
+    parts = [grads(slice(a, a + n // 4 + 1)) for a in range(0, n, n // 4 + 1)]
+    for k in range(2):
+        assert torch.equal(torch.nan_to_num(whole[k], nan=7.0),
+                           torch.nan_to_num(torch.cat([p[k] for p in parts]), nan=7.0))
