@@ -28,7 +28,7 @@
 // points, 11 partons and alpha_s on 100 x 50 knots: 934 -> 489 us FP64 and 588 ->
 // 302 us FP32 against the double-buffered kernel's default shape; 3 million
 // points, 5 partons on 150 x 60 knots, continued outside: 345 -> 125 us; 101
-// members of 200003 points FP64: 4.37 -> 1.13 ms, of 1 million FP32: 5.97 -> 2.95.
+// members of 200003 points FP64: 4.37 -> 1.10 ms, of 1 million FP32: 5.97 -> 2.95.
 #include "piece_axis.h"
 #include "set_internal.h"
 
@@ -169,8 +169,10 @@ __global__ __launch_bounds__(kRouteBlock<V>) void xfx_route_kernel(const RouteAr
         const int rs = a.raw ? nq : nq + 2;
         const size_t fs = a.raw ? (size_t)nx * nq : (size_t)(F32 ? md.slab32 : md.slab64);
         const size_t o0 = a.raw ? 0 : (size_t)rs + 1;
-        // (H rows of four x values at once, so that as many loads are in flight)
-        constexpr int H = F32 ? 4 : 2;
+        // (H rows of four x values at once, so that as many loads are in flight: 101 members
+        // of 200003 points FP64 1131 us with 2, 1103 with 4; the FP64 instance with alpha_s
+        // loses 2% of its 10 million points to what 4 does to its registers)
+        constexpr int H = F32 || !AS ? 4 : 2;
         const int urow = lane < n_u ? a.urow[lane] : 0;
         for (int u = 0; u < n_u; u += H) {
             gptr<V> g[H];
